@@ -226,12 +226,13 @@ nmm_status nmm_mla_query_path_run(const nmm_mla_query_path* qp, void* workspace,
  * [N, K] (Wt[n * ldwt + k]), the layout of a torch Linear weight and the one a dense
  * y = x . Wt^T GEMM reads, so one weight copy serves both (the paper keeps the matrix-unit
  * path's weight layout in global memory, Section IV-C; its Algorithm 1 multiplies rows by
- * columns).  Each output is the dot product of two contiguous rows: a wave streams 512 k of a
- * few Wt rows per step (two for one x row, four for more) with several steps in flight, and
- * folds its lanes at the end of the rows.  K is split (partials in
- * the workspace, combined in slice order in the same launch) only beyond 16384 / mt values,
- * mt = min(M, 4) rounded up to 1, 2 or 4; M above 4 runs in blocks of 4 rows, each reading Wt
- * again.
+ * columns).  From two rows of x on, and for one row up to K = 2048, the matrix cores take it: a
+ * workgroup owns 16 or 32 rows of Wt and all of K, reads them once for up to 32 rows of x and adds
+ * chains of two matrix instructions in fp64.  One row of a longer K streams: a wave reads 512 k of two
+ * Wt rows per step with several steps in flight, and folds its lanes at the end of the rows; K is split
+ * (partials in the workspace, combined in slice order in the same launch) only beyond 16384 values.
+ * The workspace of more rows (K beyond 16384 / mt, mt = min(M, 4) rounded up to 1, 2 or 4) is asked
+ * for and not used.
  *
  *   x, ldx      as for nmm_gemv (16-byte aligned, ldx >= K, multiple of 8).
  *   Wt, ldwt    16-byte aligned, ldwt >= K and a multiple of 8; (N-1)*ldwt + roundup(K, 8)

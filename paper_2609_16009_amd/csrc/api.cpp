@@ -289,6 +289,9 @@ nmm_status nmm_gemv_nt(int64_t M, int64_t K, int64_t N, nmm_dtype dt, const void
     if (K > 0) {
         st = validate_workspace(workspace, workspace_bytes, p.ws_bytes);
         if (st != NMM_OK) return st;
+        NtMfmaPlan m;
+        if (plan_mfma_nt(a, &m)) return launch_mfma_nt(a, m, stream);
+        if (M > 1) return NMM_ERR_SHAPE;
     }
     unsigned* tickets = static_cast<unsigned*>(workspace);
     float* part = workspace ? reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) + kTicketBytes) : nullptr;

@@ -92,13 +92,26 @@ constexpr int kKvMaxRope = 512;     // RoPE width: one pair per thread of a 256-
 struct NtPlan {
     int mt = 1, mblocks = 1;
     int r = 1, row_blocks = 1;
-    int rgroup = 1;        // rows a wave walks together (1, 2, 4 or 8; r is a multiple of it)
-    int depth = 8;         // loads in flight per lane: rgroup x steps (8, or 16 for 1-row tiles)
+    int rgroup = 1;        // rows a wave walks together (r is a multiple of it)
     int slice_k = 512, ks = 1;
     int64_t grid = 0;
     int64_t n_tickets = 0;
     size_t ws_bytes = 0;
 };
+// The transposed-weight product on the matrix cores (mfma_nt.hip): 16 nt rows of Wt per workgroup
+// and all of K, its waves taking groups of kMfmaNtGroup values of k in turn; x in blocks of 4 xr rows.
+constexpr int kMfmaNtGroup = 128;
+constexpr int64_t kMfmaNtOneRowK = 2048;   // one row takes the matrix cores up to this K
+struct NtMfmaPlan {
+    int xr = 1, mblocks = 1;   // quads of x rows per block (1, 2, 4 or 8) and blocks
+    int nt = 1, depth = 2;     // 16-row tiles of Wt per workgroup; groups in flight per wave
+    int rot = 0;               // rounds by which the next row block starts its walk later
+    int row_blocks = 1;
+    int64_t grid = 0;      // row_blocks rounded up to 8, times mblocks
+};
+bool plan_mfma_nt(const GemvArgs& a, NtMfmaPlan* p);   // false: take gemv_nt_kernel
+nmm_status launch_mfma_nt(const GemvArgs& a, const NtMfmaPlan& p, void* stream);
+
 nmm_status validate_gemv_nt(const GemvArgs& a);
 nmm_status plan_gemv_nt(int64_t M, int64_t K, int64_t N, NtPlan* p);
 

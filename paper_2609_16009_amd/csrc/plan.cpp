@@ -277,7 +277,9 @@ nmm_status plan_gemv(int64_t batch, int64_t M, int64_t K, int64_t N, int dt, int
 // ---------------------------------------------------------------------------------------------
 // The transposed-weight GEMV.  x's K-slice is staged in LDS as 16-bit values (at most
 // kXStageBytes), so a slice holds at most 16384 / mt values of k; rows are dealt so that at
-// least one workgroup per CU streams (4 r rows each, r at most 8).
+// least one workgroup per CU streams (4 r rows each, r at most 8).  The kernel runs one row (mt 1);
+// the plans of more rows, which the matrix cores take, still say which sizes are refused and what
+// workspace a call brings.
 // ---------------------------------------------------------------------------------------------
 nmm_status validate_gemv_nt(const GemvArgs& a) {
     if (a.dt != NMM_F16 && a.dt != NMM_BF16) return NMM_ERR_DTYPE;
@@ -318,18 +320,10 @@ nmm_status plan_gemv_nt(int64_t M, int64_t K, int64_t N, NtPlan* p) {
     // measured faster for W_UQ's [24576, 1536] (768 workgroups) than 24 rows per wave
     int r = static_cast<int>(std::min<int64_t>(8, std::max<int64_t>(1, N / (4 * target_rb))));
     r = static_cast<int>(std::min<int64_t>(32, std::max<int64_t>(1, tuned("NMM_NT_ROWS", r))));
-    // rows per load step (rgroup) times steps in flight is 8 loads per lane.  With eight rows per
-    // step only one step is in flight, so the next step's loads wait for this step's multiply-adds;
-    // with one row per step x is read from LDS for every load.  Measured on MI355X: one-row tiles
-    // take two rows per step (four steps in flight; W_O [7168, 16384] 39.0 against 41.7 us with
-    // eight, W_UQ [24576, 1536] 14.7 against 15.1), taller tiles, whose x reads per step grow with
-    // MT, four (two steps in flight; at M = 2 W_O 46.6 against 49.1, W_UQ 15.6 against 16.7, down
-    // [2112, 7168] 12.2 against 13.5 with its rows per wave raised from 2 to 4; at M = 4 W_O 55.8
-    // against 61.7).  One row per wave (small N) keeps one.
+    // rows per load step (rgroup) times steps in flight is 8 loads per lane: two rows per step keep
+    // four steps in flight and read x from LDS once for two loads (W_O [7168, 16384] 39.0 us against
+    // 41.7 with eight rows and one step, 49.7 with one row).  One row per wave (small N) keeps one.
     q.rgroup = r < 2 ? 1 : q.mt == 1 ? 2 : 4;
-    const int rg = tuned("NMM_NT_GROUP", q.rgroup);
-    if (rg == 1 || rg == 2 || rg == 4 || rg == 8) q.rgroup = rg;
-    q.depth = (q.mt == 1 && tuned("NMM_NT_DEPTH", 8) == 16) ? 16 : 8;
     q.r = (r + q.rgroup - 1) / q.rgroup * q.rgroup;
     const int64_t rb = cdiv(N, 4 * q.r);
     if (rb >= kLimit) return NMM_ERR_SHAPE;
@@ -343,6 +337,45 @@ nmm_status plan_gemv_nt(int64_t M, int64_t K, int64_t N, NtPlan* p) {
     }
     *p = q;
     return NMM_OK;
+}
+
+// The matrix-core form of the transposed-weight product, or false where the one-row GEMV is the
+// better one.  Measured on MI355X (GPU time, W rotated over three copies):
+//  * from two rows on always: W_O [7168, 16384] at 2 / 4 / 16 / 32 rows 40 / 40 / 41 / 52 us against
+//    48 / 53 / 172 / 332 for the GEMV (in blocks of 4 rows); [576, 7168] 7.3 / 7.8 / 10.3 / 13.4
+//    against 8.2 / 17.3 / 19.5 / 27.5; [512, 512] 2.7 / 2.8 / 3.1 / 3.9 against 4.4 / 5.1 / 6.0 / 6.0;
+//  * one row up to K = 2048: [512, 512] 2.75 against 4.17, [1536, 1536] 3.95 against 4.84, W_UQ
+//    [24576, 1536] 13.9 against 14.6, [7168, 2048] 7.7 against 8.6; past that the GEMV's 1 KB rows
+//    win where rows are few or not 256-byte aligned ([576, 7168] 6.6 against 7.5, [5003, 4099] 11.4
+//    against 12.0) and the two are within 5 % elsewhere.
+bool plan_mfma_nt(const GemvArgs& a, NtMfmaPlan* p) {
+    const int64_t M = a.M, K = a.K, N = a.N;
+    if (M < 1 || K < 1 || N < 1 || (M == 1 && K > kMfmaNtOneRowK)) return false;
+    NtMfmaPlan q;
+    q.xr = M <= 4 ? 1 : M <= 8 ? 2 : M <= 16 ? 4 : 8;
+    // x rows of a block are addressed through one 32-bit buffer resource (4 rows always fit)
+    if (((std::min<int64_t>(M, 4 * q.xr) - 1) * a.ldx + rup(K, 8)) * 2 >= kLimit) q.xr = 1;
+    q.mblocks = static_cast<int>(cdiv(M, 4 * q.xr));
+    // two 16-row tiles of Wt per wave halve the x traffic from L2, which counts from 16 rows on: W_O 41
+    // against 46 us at 16 rows and 52 against 62 at 32, [5003, 4099] 18.5 against 22.8 at 32; while the
+    // grid still has over half a workgroup per CU (at fewer, [2112, 7168] 15.3 against 11.2)
+    q.nt = q.xr >= 4 && cdiv(N, 32) >= 150 ? 2 : 1;
+    q.row_blocks = static_cast<int>(cdiv(N, 16 * q.nt));
+    // one workgroup per CU at most: a third group in flight (up to 8 rows; [2112, 7168] 8.6 against 9.1
+    // us at 4); with more workgroups than CUs the smaller ring lets more of them share a CU (W_UQ at one
+    // row 13.9 against 16.4)
+    q.depth = q.row_blocks <= 256 && q.xr <= 2 ? 3 : 2;
+    // Rows whose 16 nt-row blocks lie a multiple of 256 KB apart meet on the same memory channels when
+    // all workgroups walk k in step, so block b starts its walk b * rot rounds on.  The shift that helps
+    // lies 2^9 or 2^7 (not 2^8) under the block stride: a stride of 512 KB takes 1 round of 1 KB, 256 KB
+    // takes 2 ([7168, 16384] 40.4 against 46.2 us, [4096, 16384] 26.1 against 31.5, [8192, 8192] 26.0
+    // against 26.9; the other shift 53, 38 and 37 us).
+    const int64_t stride = int64_t(16) * q.nt * a.ldw * 2;
+    q.rot = stride % (1 << 19) == 0 ? 1 : stride % (1 << 18) == 0 ? 2 : 0;
+    q.grid = rup(q.row_blocks, 8) * q.mblocks;
+    if (q.grid >= kLimit) return false;
+    *p = q;
+    return true;
 }
 
 }  // namespace nmm

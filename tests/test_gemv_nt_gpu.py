@@ -5,7 +5,7 @@ The oracle takes W as [K, N]; the tests draw W that way and hand the GPU its tra
 expected values are the same plain product as for nmm_gemv.  Floating-point cases meet the fp32
 bar, integer-valued cases match bit for bit.  Shapes cover the decode chain's matrices as torch
 stores them, split and unsplit K, ragged K (row padding filled with NaN, which must not reach the
-sums) and ragged N, M above the 4-row block, fp16, and K = 0.
+sums) and ragged N, the edges of the matrix-core tiles, fp16, and K = 0.
 """
 import numpy as np
 import pytest
@@ -78,6 +78,39 @@ def test_nt_random_shapes_integer_exact(case):
     M, K, N, dt, ldx, ldwt = case
     c = syn.gemv_case(800 + M + K % 83, M, K, N, dt, integer=True, ldx=ldx, name=f"nt_random_{M}x{K}x{N}")
     check_nt(c, ldwt, ldy=N + 5)
+
+
+@pytest.mark.parametrize("M", [1, 2, 4, 5, 8, 9, 16, 17, 32, 33])
+@pytest.mark.parametrize("K,N,ldwt", [(127, 17, 128), (128, 15, 128), (513, 33, 520), (2048, 47, 2048),
+                                      (300, 4800, 304), (8192, 40, 8192), (1100, 20, 16384)])
+def test_nt_matrix_core_edges_integer_exact(M, K, N, ldwt):
+    # the row tiles of x (4, 8, 16, 32), one and two tiles of Wt, groups of 128 k, a block stride that
+    # shifts where each block starts; NaN past K and N must not reach a sum
+    for dt in (syn.BF16, syn.F16):
+        c = syn.gemv_case(900 + M + K % 97, M, K, N, dt, integer=True, ldx=(K + 15) // 8 * 8, name=f"nt_edge_{M}x{K}x{N}")
+        check_nt(c, ldwt, ldy=N + 3)
+
+
+def test_nt_matrix_cores_keep_subnormals():
+    # fp16 subnormal inputs, and bf16 products below the fp32 normal range, are exact
+    for dt, a, b in ((torch.float16, 2.0 ** -24, 1.0), (torch.bfloat16, 2.0 ** -70, 2.0 ** -70)):
+        x, Wt = torch.full((4, 64), a, device="cuda").to(dt), torch.full((16, 64), b, device="cuda").to(dt)
+        y = torch.empty((4, 16), dtype=torch.float32, device="cuda")
+        nmm.nmm_gemv_nt(x, Wt, y)
+        torch.cuda.synchronize()
+        assert torch.all(y.double() == 64 * a * b)
+
+
+def test_nt_far_apart_x_rows():
+    # x rows 2^28 elements apart: five rows pass one 32-bit buffer resource, so blocks of 4 rows run
+    M, K, N, ldx = 5, 64, 24, 1 << 28
+    x = torch.empty((M - 1) * ldx + K, dtype=torch.bfloat16, device="cuda").as_strided((M, K), (ldx, 1))
+    Wt = torch.randint(-3, 4, (N, K), device="cuda").to(torch.bfloat16)
+    x.copy_(torch.randint(-3, 4, (M, K), device="cuda"))
+    y = torch.empty((M, N), dtype=torch.float32, device="cuda")
+    nmm.nmm_gemv_nt(x, Wt, y)
+    torch.cuda.synchronize()
+    assert torch.equal(y.double().cpu(), x.double().cpu() @ Wt.double().cpu().T)
 
 
 def test_nt_agrees_with_the_row_major_path_within_the_bar():

@@ -288,6 +288,52 @@ def test_gemv_nt_launch_stays_in_bounds(M, K, N, ldx, ldwt):
                             assert pbase + (mt - 1) * R + wave * r + i < part_floats
 
 
+@pytest.mark.parametrize("M,K,N,ldx,ldwt", [(2, 13, 8, 16, 16), (5, 777, 300, 784, 800), (16, 4099, 5003, 4104, 4104),
+                                            (33, 1000, 4900, 1000, 1000), (1, 2048, 47, 2048, 2048), (4, 129, 33, 136, 136),
+                                            (32, 128, 16, 128, 128), (16, 16383, 65521, 16384, 16384)])
+def test_mfma_nt_launch_covers_every_chunk_in_bounds(M, K, N, ldx, ldwt):
+    """mfma_nt_kernel: a wave's LDS-direct loads (4 rows x 16 chunks each, chunk c of row r in slot
+    c ^ (r % 16)) take every 16-byte chunk of a workgroup's rows of Wt and x exactly once, whatever the
+    round the block starts at, inside both extents; and every fragment read finds row j's chunk
+    4 s + g of its group."""
+    xr = 1 if M <= 4 else 2 if M <= 8 else 4 if M <= 16 else 8
+    nt = 2 if xr >= 4 and -(-N // 32) >= 150 else 1
+    stride = 16 * nt * ldwt * 2
+    rot = 1 if stride % (1 << 19) == 0 else 2 if stride % (1 << 18) == 0 else 0
+    NW, group = 4, 128
+    groups = -(-K // group)
+    rounds = -(-groups // NW)
+    row_blocks, mblocks = -(-N // (16 * nt)), -(-M // (4 * xr))
+    lane = np.arange(64)
+    for rb in sorted({0, row_blocks // 2, row_blocks - 1}):
+        start = rb * rot % rounds
+        seq = [wave + (r + start - (rounds if r + start >= rounds else 0)) * NW for r in range(rounds) for wave in range(NW)]
+        assert sorted(g for g in seq if g < groups) == list(range(groups))      # every group once
+        for rows, total, ld in ((16 * nt, N - rb * 16 * nt, ldwt), (4 * xr, M - (mblocks - 1) * 4 * xr, ldx)):
+            seen = np.zeros((rows, 16), int)
+            for q in range(rows // 4):
+                r, c = 4 * q + lane // 16, (lane % 16) ^ ((4 * q + lane // 16) & 15)
+                seen[r, c] += 1
+                for g in (0, groups - 1):
+                    k = g * group + 8 * c
+                    ok = (r < total) & (k < K)
+                    first = rb * 16 * nt if ld == ldwt and rows == 16 * nt else 0
+                    off = (first + r) * ld * 2 + 2 * k
+                    extent = ((first + total - 1) * ld + (K + 7) // 8 * 8) * 2
+                    assert np.all(off[ok] + 16 <= extent) and extent < 2 ** 31
+            assert np.all(seen == 1)
+    slot = lambda r, c: 256 * r + 16 * (c ^ (r & 15))       # byte of chunk c of row r in a tile
+    g, j = lane >> 4, lane & 15
+    for s in range(4):
+        for rows in (16, 4, 8):                             # x tiles of fewer rows repeat them
+            jr = j & (rows - 1)
+            addr = (jr * 256 + ((g ^ jr) * 16)) ^ (64 * s)
+            assert np.array_equal(addr, slot(jr, 4 * s + g)) and np.all(addr + 16 <= rows * 256)
+        for first in range(0, 64, 16):                      # 16 rows of one g: 16 different columns
+            a = ((j * 256 + ((g ^ j) * 16)) ^ (64 * s))[first:first + 16]
+            assert len(set((a // 16) % 16)) == 16
+
+
 @pytest.mark.parametrize("case", syn.random_batched_shapes(), ids=lambda c: "x".join(map(str, c)))
 def test_random_batched_shapes_stay_in_bounds(case):
     """The seeded sweep of the batched GEMV the GPU tests run (synthetic.random_batched_shapes)."""
