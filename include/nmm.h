@@ -3,7 +3,7 @@
  *
  * The library computes narrow matrix multiplications y = x . W in which x has only a few rows
  * (any M on either path; AUTO streams W on the vector units for one row and uses the matrix
- * cores from three rows on, and from two where that needs no K-split), at the shapes of DeepSeek-V3
+ * cores from three rows on, and from two where that needs no K-split or W is a batch), at the shapes of DeepSeek-V3
  * Multi-head Latent Attention single-token decode.  The operation is the paper's problem
  * statement C = A x B with A in R^{M x K}, B in R^{K x N}, narrow when min(M, N) = 1
  * (Section II-E "Problem Statement"; Section III-A, Condition 2 "Narrow Dimension"), widened to
@@ -72,8 +72,9 @@ typedef enum { NMM_F16 = 1, NMM_BF16 = 2 } nmm_dtype;
 
 /* Which kernel family computes the product.  AUTO picks from measured crossovers: the
  * streaming GEMV for M = 1, the MFMA (matrix-core) path for M >= 3, and at M = 2 the MFMA path
- * where its plan has a single K-slice (e.g. W_UQ [1536, 24576]), the GEMV otherwise (single
- * matrices; batched calls always stream).  GEMV and MFMA force a family.  NMM_PATH_MFMA with
+ * where its plan has a single K-slice (e.g. W_UQ [1536, 24576]), the GEMV otherwise.  Batched calls
+ * take a matrix-core form from two rows on (K <= 2048, or 256 workgroups and more), and at one row
+ * where K <= 256 and the grid is small.  GEMV and MFMA force a family; NMM_PATH_MFMA with
  * batch > 1 is NMM_ERR_PATH.  The choice depends on the shape only. */
 typedef enum { NMM_PATH_AUTO = 0, NMM_PATH_GEMV = 1, NMM_PATH_MFMA = 2 } nmm_path;
 
@@ -461,7 +462,9 @@ nmm_status nmm_workspace_init(void* workspace, size_t workspace_bytes, void* str
 /*
  * The host-side partition the library would launch for these sizes (a pure function: no GPU
  * access).  Algorithm 2's init stage (Section IV-E) sizes its executor pool from the core
- * count; here the plan sizes a grid of workgroups for 256 compute units.
+ * count; here the plan sizes a grid of workgroups for 256 compute units.  For a batch this is the
+ * streaming partition, also where AUTO's launch takes the matrix cores (which need no workspace; the
+ * call still asks for this partition's).
  */
 typedef struct {
     int32_t path;            /* NMM_PATH_GEMV or NMM_PATH_MFMA */

@@ -54,6 +54,7 @@ nmm_status gemv_common(const GemvArgs& a, int path, void* ws, size_t ws_bytes, v
     if (a.K > 0) {
         st = validate_workspace(ws, ws_bytes, p.ws_bytes);
         if (st != NMM_OK) return st;
+        if (path == NMM_PATH_AUTO && heads_on_mfma(a.batch, a.M, a.K, a.N)) return launch_mfma_heads(a, stream);
     }
     return gemv_launch(a, p, ws, stream);
 }

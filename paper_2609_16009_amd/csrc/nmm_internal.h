@@ -36,7 +36,9 @@ constexpr int64_t kTicketBytes = kMaxTickets * 4;
 // Matrix-core path (mfma_gemv.hip): 128-column panels, W staged 64 rows at a time.
 constexpr int kMfmaPanelCols = 128;
 constexpr int kMfmaStageRows = 64;
+constexpr int kHeadsCols = 64;             // columns per workgroup of the batched matrix-core kernel
 constexpr int kMfmaTargetGrid = 256;      // the matrix-core plan splits K until about this many workgroups
+constexpr int64_t kMfmaLongK = 2048;
 constexpr int kMfmaMinMDefault = 3;        // AUTO uses the matrix cores from this many rows on
 
 struct GemvPlan {
@@ -146,6 +148,9 @@ size_t gemv_kv_lds_bytes(const GemvPlan& p, int kv, int rope);
 
 nmm_status launch_mfma(const GemvArgs& a, const GemvPlan& p, unsigned* tickets, float* part, void* stream);
 size_t mfma_lds_bytes(const GemvPlan& p);
+// A batch on the matrix cores (mfma_heads.hip): which AUTO calls take it, and the launch.
+bool heads_on_mfma(int64_t batch, int64_t M, int64_t K, int64_t N);
+nmm_status launch_mfma_heads(const GemvArgs& a, void* stream);
 int device_cus();   // compute units of the current device
 
 // The decode chain's W_UK -> W_UV pair in one launch, one workgroup per head (bf16, M = 1):

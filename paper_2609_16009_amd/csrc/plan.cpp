@@ -147,12 +147,12 @@ nmm_status plan_gemv(int64_t batch, int64_t M, int64_t K, int64_t N, int dt, int
     if (batch < 0 || M < 0 || K < 0 || N < 0 || M >= kLimit || K >= kLimit || N >= kLimit)
         return NMM_ERR_SHAPE;
     GemvPlan q;
-    // AUTO (single matrices; batched calls always stream): the streaming GEMV for one row, the
-    // matrix cores from kMfmaMinMDefault rows on.  At two rows the matrix-core launch wins only
-    // where its plan needs no K-split: its split-K tail (16-row partials) costs more than the
-    // GEMV's second row.  Measured on MI355X: W_UQ [1536, 24576] (one slice) 15.8 against
-    // 16.3 us; W_O [16384, 7168] (4 slices) 42.2 against 41.1; down [7168, 2112] (16 slices)
-    // 14.0 against 10.3.
+    // AUTO for a single matrix: the streaming GEMV for one row, the matrix cores from
+    // kMfmaMinMDefault rows on.  At two rows the matrix-core launch wins only where its plan needs no
+    // K-split: its split-K tail costs more than the GEMV's second row.  Measured on MI355X: W_UQ [1536,
+    // 24576] (one slice) 15.4 against 16.3 us; W_O [16384, 7168] (4 slices) 40.5 against 39.8; down
+    // [7168, 2112] (15 slices) 10.5 against 9.7.  A batch has the streaming plan; whether its
+    // launch takes the matrix cores instead is heads_on_mfma's.
     if (path == NMM_PATH_AUTO) {
         const int64_t mfma_min_m = tuned("NMM_MFMA_MIN_M", kMfmaMinMDefault);
         path = NMM_PATH_GEMV;
@@ -273,6 +273,22 @@ nmm_status plan_gemv(int64_t batch, int64_t M, int64_t K, int64_t N, int dt, int
     return NMM_OK;
 }
 
+
+// Whether AUTO gives a batch to the matrix cores.  Measured on MI355X (batches of 8 / 32 / 128 heads):
+//  * from two rows on: [128, 512] at 2 rows 3.1 / 3.6 / 6.0 us against 4.9 / 5.2 / 6.1 for the GEMV, at
+//    4 rows 3.1 / 3.6 / 6.0 against 7.2 / 8.9 / 8.2, at 16 rows 3.2 / 3.8 / 7.4 against 15 / 21 / 21.5;
+//    [512, 128] at 4 rows 4.6 / 4.7 / 5.9 against 7.2 / 7.7 / 8.0;
+//  * at one row where K is short and the grid small, so that the GEMV has little to stream: [128, 512]
+//    3.1 / 3.6 against 4.3 / 4.6 for 8 and 32 heads, but 5.8 against 5.4 for 128; [512, 128] 4.5 / 4.7 /
+//    5.8 against 4.4 / 4.4 / 5.9.
+// All of K is one workgroup's, so a long K with few workgroups stays on the GEMV, which splits it.
+bool heads_on_mfma(int64_t batch, int64_t M, int64_t K, int64_t N) {
+    if (batch <= 1 || M <= 0 || K <= 0 || N <= 0) return false;
+    const int64_t groups = batch * cdiv(N, kHeadsCols);          // workgroups per row block
+    if (groups * cdiv(M, 16) >= kLimit / kThreads) return false;
+    if (M == 1) return K <= 256 && groups <= 512;
+    return K <= kMfmaLongK || groups >= 256;
+}
 
 // ---------------------------------------------------------------------------------------------
 // The transposed-weight GEMV.  x's K-slice is staged in LDS as 16-bit values (at most

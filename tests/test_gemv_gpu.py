@@ -316,6 +316,48 @@ def test_batched_random_shapes_integer_exact(case):
     assert_parity(y, y_ref, a_ref, integer=True, what=f"batched {B}x{M}x{K}x{N}")
 
 
+@pytest.mark.parametrize("B,M", [(2, 1), (300, 1), (3, 2), (2, 15), (3, 16), (2, 17), (2, 33)])
+@pytest.mark.parametrize("K,N", [(1, 1), (31, 63), (128, 64), (129, 65), (256, 700), (513, 128), (2048, 9)])
+def test_batched_matrix_core_edges_integer_exact(B, M, K, N):
+    # AUTO's batched matrix-core launch at the edges of its row, column and K tiles: NaN in every
+    # padding value, outputs on and off 16-byte rows, fp32 and bf16 (either tie rule), alone and together
+    rng = np.random.default_rng(B * 31 + M * 7 + K + N)
+    K8, N8 = (K + 7) // 8 * 8, (N + 7) // 8 * 8
+    for dt, ldy in ((syn.BF16, N8 + 4), (syn.F16, N + 1)):
+        x = np.stack([syn.padded(a, K8) for a in syn.int_bits(rng, (B, M, K), dt)])
+        W = np.stack([syn.padded(a, N8 + 8) for a in syn.int_bits(rng, (B, K, N), dt)])
+        xd, Wd = dev16(x, dt), dev16(W, dt)
+        y_ref, a_ref = oracle.batched_gemv(x, W, dt, N=N)
+        y = torch.full((B, M, ldy), float("nan"), dtype=torch.float32, device="cuda")
+        nmm.nmm_batched_gemv(xd, Wd, y, N=N)
+        yb = torch.full((B, M, ldy), float("nan"), dtype=torch.bfloat16, device="cuda")
+        y2 = torch.empty((B, M, N), dtype=torch.float32, device="cuda")
+        nmm.nmm_batched_gemv_bf16(xd, Wd, yb, y=y2, N=N, round=nmm.NMM_ROUND_AWAY)
+        yc = torch.empty((B, M, N), dtype=torch.bfloat16, device="cuda")
+        nmm.nmm_batched_gemv_bf16(xd, Wd, yc, N=N)
+        torch.cuda.synchronize()
+        assert_parity(y[:, :, :N], y_ref, a_ref, integer=True, what=f"heads {B}x{M}x{K}x{N}")
+        assert torch.equal(y2, y[:, :, :N]) and torch.equal(yc, y2.to(torch.bfloat16))
+        assert torch.isnan(y[:, :, N:]).all() and torch.isnan(yb[:, :, N:]).all(), "columns past N were written"
+        away = oracle.round_bf16(y2.cpu().numpy(), mode=1)
+        assert np.array_equal(yb[:, :, :N].contiguous().view(torch.int16).cpu().numpy().view(np.uint16), away)
+
+
+@pytest.mark.parametrize("K", [128, 100, 1024])
+def test_batched_matrix_cores_agree_with_the_stream(K):
+    # AUTO against the streaming form over strided slices, a broadcast weight and both 16-bit types
+    g = torch.Generator(device="cuda").manual_seed(K)
+    for dt in (torch.bfloat16, torch.float16):
+        x = torch.randn((6, 5, 2 * K + 56), generator=g, device="cuda").to(dt)[:, 1:4, :K]
+        W = (torch.randn((1, K, 208), generator=g, device="cuda") / K ** 0.5).to(dt).expand(6, K, 208)
+        a, b = (torch.empty((6, 3, 200), device="cuda") for _ in range(2))
+        nmm.nmm_batched_gemv(x, W, a, N=200)
+        nmm.nmm_batched_gemv(x, W, b, N=200, path=nmm.NMM_PATH_GEMV)
+        torch.cuda.synchronize()
+        # both sum exact products in fp32 or wider: K roundings of 2^-24 at most, against sums near 1
+        assert (a - b).abs().max().item() < K * 2.0 ** -24 * 8
+
+
 # ------------------------------------------------------------------ matrix-core path
 
 @pytest.mark.parametrize("M", [1, 2, 3, 4, 5, 8, 16, 17, 32])

@@ -334,6 +334,54 @@ def test_mfma_nt_launch_covers_every_chunk_in_bounds(M, K, N, ldx, ldwt):
             assert len(set((a // 16) % 16)) == 16
 
 
+@pytest.mark.parametrize("M,K,N,ldx,ldw", [(4, 128, 512, 128, 512), (1, 1, 1, 8, 8), (17, 129, 65, 136, 72),
+                                           (33, 513, 700, 520, 704), (2, 2048, 9, 2048, 16)])
+def test_mfma_heads_launch_covers_every_chunk_in_bounds(M, K, N, ldx, ldw):
+    """mfma_heads_kernel: a wave's LDS-direct loads take every 16-byte chunk of a workgroup's 64 columns
+    of W (8 rows x 8 chunks a load) and of its x tile (16 rows x 4 chunks) exactly once and inside both
+    extents, and every fragment read finds its chunk: W row 8 g + j / 4 (+ 4), columns 16 t + 4 (j % 4),
+    and x row j, chunk g."""
+    lane = np.arange(64)
+    g, j = lane >> 4, lane & 15
+    f = lambda r: 2 * (((r >> 1) & 1) + 2 * ((r >> 3) & 1))
+    MT = 1 if M <= 16 else 2
+    groups = -(-K // 32)
+    rounds = -(-groups // 4)
+    assert sorted(w + 4 * r for r in range(rounds) for w in range(4))[:groups] == list(range(groups))
+    for panel in {0, -(-N // 64) - 1}:
+        n0, valid = panel * 64, min(8, (N - panel * 64 + 7) // 8)
+        seen = np.zeros((32, 8), int)
+        for q in range(4):
+            r = 8 * q + (lane >> 3)
+            c = (lane & 7) ^ (2 * ((((lane >> 3) >> 1) & 1) + 2 * (q & 1)))
+            assert np.array_equal(c, (lane & 7) ^ f(r))
+            seen[r, c] += 1
+            for grp in (0, groups - 1):
+                k = 32 * grp + r
+                ok = (k < K) & (c < valid)
+                assert np.all((k * ldw * 2 + n0 * 2 + 16 * c)[ok] + 16 <= ((K - 1) * ldw + (N + 7) // 8 * 8) * 2)
+        assert np.all(seen == 1)
+    mrows = M - (-(-M // (16 * MT)) - 1) * 16 * MT
+    seen = np.zeros((16 * MT, 4), int)
+    for t in range(MT):
+        r, c = 16 * t + (lane >> 2), (lane & 3) ^ (((lane >> 2) >> 2) & 3)
+        seen[r, c] += 1
+        k = 32 * (groups - 1) + 8 * c
+        ok = (r < mrows) & (k < K)
+        assert np.all((r * ldx * 2 + 2 * k)[ok] + 16 <= ((mrows - 1) * ldx + (K + 7) // 8 * 8) * 2)
+    assert np.all(seen == 1)
+    base = (8 * g + (j >> 2)) * 128 + 16 * ((2 * ((j >> 3) + 2 * (g & 1))) ^ ((j & 3) >> 1)) + 8 * (j & 1)
+    for t in range(4):
+        for half in range(2):
+            r = 8 * g + (j >> 2) + 4 * half
+            chunk = 2 * t + ((j & 3) >> 1)
+            assert np.array_equal((base ^ (32 * t)) + 512 * half, r * 128 + 16 * (chunk ^ f(r)) + 8 * (j & 1))
+            for first in range(0, 64, 16):                  # 16 lanes of one g: 16 different 8-byte columns
+                assert len(set((((base ^ (32 * t)) // 8) % 32)[first:first + 16])) == 16
+    for first in range(0, 64, 16):
+        assert len(set(((j * 64 + 16 * (g ^ ((j >> 2) & 3))) // 16 % 16)[first:first + 16])) == 16
+
+
 @pytest.mark.parametrize("case", syn.random_batched_shapes(), ids=lambda c: "x".join(map(str, c)))
 def test_random_batched_shapes_stay_in_bounds(case):
     """The seeded sweep of the batched GEMV the GPU tests run (synthetic.random_batched_shapes)."""
