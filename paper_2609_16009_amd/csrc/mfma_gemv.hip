@@ -16,17 +16,24 @@
 //    hold consecutive columns).  x travels with W instead of being staged for the whole slice
 //    up front, so no workgroup waits for its x before its W stream starts and the slice length
 //    is not bounded by LDS.
-//  * Wave w owns the column tiles 2w and 2w+1 of the panel, so no cross-wave reduction is needed.
-//  * K-slices are combined exactly like the GEMV's: device-scope atomic partial stores, a
-//    ticket per panel, and the last workgroup sums the slices in order.
+//  * Wave w owns the column tiles 2w and 2w+1 of the panel, so no cross-wave reduction is needed.  W
+//    is the A operand and x the B operand, so a lane ends with 4 consecutive columns of one row and
+//    stores 16 bytes at a time.
+//  * Sums: the two MFMAs of a stage chain in fp32 from zero and are added in fp64; the K-slices are
+//    added in fp64 as well.  Relative 2-norm error 5e-8 at any K; one fp32 chain over K: 2.3e-7 at
+//    K = 1536, 8.0e-7 at 16384.
+//  * K-slices are combined like the GEMV's: device-scope stores of the slice's M rows (not of the
+//    whole 16- or 32-row tile), a ticket per panel, and the last workgroup sums the slices in order,
+//    16 bytes a load.  The tail is what bounds short weights: [7168, 2112] at 3 rows 10.5 us (13.3
+//    with 4-byte partials of all 16 rows and 16 slices), [7168, 576] 8.0 (9.8).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cstdint>
 
-#include "bf16_cast.h"
 #include "handoff.h"
 #include "nmm_internal.h"
+#include "out4.h"
 
 namespace nmm {
 namespace {
@@ -42,6 +49,7 @@ typedef __attribute__((address_space(3))) fp16x4 lds_f16x4;
 
 constexpr int kRsrcWord3 = 0x00020000;
 constexpr int kLoadNT = 2;
+constexpr int kDevice = 16;                    // sc1: device scope (past the XCD's L2)
 constexpr uint32_t kOutOfRange = 0x80000000u;
 constexpr int kWStride = kMfmaPanelCols + 8;   // LDS row stride of a W stage (elements)
 constexpr int kXStride = kMfmaStageRows + 8;   // LDS row stride of an x stage (elements)
@@ -67,17 +75,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, ui
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, kRsrcWord3);
 }
 
-// An output: fp32 y only (BF false), or the bf16 copy and, when y is not null, y as well.
-template <bool BF>
-__device__ __forceinline__ void put_y(const MParams& p, int m, int n, float v) {
-    if constexpr (BF) {
-        if (p.y) p.y[int64_t(m) * p.ldy + n] = v;
-        p.ybf[int64_t(m) * p.ldyb + n] = to_bf16_mode(v, p.away);
-    } else {
-        p.y[int64_t(m) * p.ldy + n] = v;
-    }
-}
-
 template <int DT>
 __device__ __forceinline__ f32x4 mfma(i32x4 a, i32x4 b, f32x4 c) {
     if constexpr (DT == NMM_BF16)
@@ -86,10 +83,10 @@ __device__ __forceinline__ f32x4 mfma(i32x4 a, i32x4 b, f32x4 c) {
         return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
 }
 
-// B operand of one 16-column tile for 32 k-rows starting at `row0` of the LDS stage: lane
+// A operand (W transposed) of one 16-column tile for 32 k-rows starting at `row0` of the LDS stage: lane
 // (g = lane/16, j = lane%16) receives W[row0 + 8g .. + 7][col0 + j] via two transposing reads.
 template <int DT>
-__device__ __forceinline__ i32x4 load_b(const uint16_t* wst, int row0, int col0, int g, int j) {
+__device__ __forceinline__ i32x4 load_w(const uint16_t* wst, int row0, int col0, int g, int j) {
     const uint16_t* base = wst + (row0 + 8 * g + (j >> 2)) * kWStride + col0 + 4 * (j & 3);
     uint2 lo, hi;
     if constexpr (DT == NMM_BF16) {
@@ -154,16 +151,19 @@ __global__ __launch_bounds__(kThreads) void mfma_gemv_kernel(const MParams p) {
         xreg[d] = __builtin_amdgcn_raw_buffer_load_b128(xr, x_off(d), 0, 0);
     }
 
-    f32x4 acc[MTILES][2];
+    double acc[MTILES][2][4];
 #pragma unroll
     for (int mt = 0; mt < MTILES; ++mt)
 #pragma unroll
-        for (int t = 0; t < 2; ++t) acc[mt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[mt][t][i] = 0.0;
 
     // one stage: registers to LDS buffer (s & 1), reload with stage s + D, then the MFMAs.  A
     // wave that writes buffer (s & 1) has passed the barrier of stage s - 1, so every wave has
     // finished reading stage s - 2 from it.
-    auto stage = [&](int s, i32x4 (&wd)[4], i32x4& xd) {
+    f32x4 part[MTILES][2];
+    auto stage = [&](int s, i32x4 (&wd)[4], i32x4& xd, bool first, bool last) {
         uint16_t* wst = smem + (s & 1) * kStage;
         uint16_t* xst = wst + kMfmaStageRows * kWStride;
 #pragma unroll
@@ -183,53 +183,73 @@ __global__ __launch_bounds__(kThreads) void mfma_gemv_kernel(const MParams p) {
         xd = __builtin_amdgcn_raw_buffer_load_b128(xr, x_off(s + D), 0, 0);
         __builtin_amdgcn_sched_barrier(0);
         __syncthreads();
+        // the 32-row steps of a chain run in fp32 from zero, then add to the fp64 sums
 #pragma unroll
         for (int kk = 0; kk < kMfmaStageRows / 32; ++kk) {
-            i32x4 a[MTILES];
+            i32x4 x[MTILES];
 #pragma unroll
             for (int mt = 0; mt < MTILES; ++mt)
-                a[mt] = *reinterpret_cast<const i32x4*>(xst + (16 * mt + j) * kXStride + 32 * kk + 8 * g);
+                x[mt] = *reinterpret_cast<const i32x4*>(xst + (16 * mt + j) * kXStride + 32 * kk + 8 * g);
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
-                const i32x4 b = load_b<DT>(wst, 32 * kk, 16 * (2 * wave + t), g, j);
+                const i32x4 w = load_w<DT>(wst, 32 * kk, 16 * (2 * wave + t), g, j);
 #pragma unroll
-                for (int mt = 0; mt < MTILES; ++mt) acc[mt][t] = mfma<DT>(a[mt], b, acc[mt][t]);
+                for (int mt = 0; mt < MTILES; ++mt)
+                    part[mt][t] = mfma<DT>(w, x[mt], kk == 0 && first ? f32x4{0.f, 0.f, 0.f, 0.f} : part[mt][t]);
             }
         }
+        if (last) {
+#pragma unroll
+            for (int mt = 0; mt < MTILES; ++mt)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[mt][t][i] += double(part[mt][t][i]);
+        }
     };
+    // a chain is one stage, or the D stages of an iteration for 32 rows, whose sums are twice as many
+    constexpr bool kLong = MTILES == 2;
     int s0 = 0;
     for (; s0 + D <= stages; s0 += D) {
 #pragma unroll
-        for (int d = 0; d < D; ++d) stage(s0 + d, wreg[d], xreg[d]);
+        for (int d = 0; d < D; ++d) stage(s0 + d, wreg[d], xreg[d], !kLong || d == 0, !kLong || d == D - 1);
     }
 #pragma unroll
     for (int d = 0; d + 1 < D; ++d)
-        if (s0 + d < stages) stage(s0 + d, wreg[d], xreg[d]);
+        if (s0 + d < stages) stage(s0 + d, wreg[d], xreg[d], true, true);
 
-    // ---- outputs: lane (g, j) holds rows 4g+i of its tiles, column j
+    // ---- outputs: lane (g, j) holds columns 4 g .. + 3 of row j of its tiles
     const int64_t pbase = ((int64_t(mb) * p.panels + panel) * p.ks) * (int64_t(MT) * kMfmaPanelCols);
+    const bool wide = wide_f32(p.y, p.ldy, 0), wide_b = BF && wide_bf16(p.ybf, p.ldyb, 0);
+    auto put = [&](int m, int n, const f32x4 f) {
+        const float v[4] = {f[0], f[1], f[2], f[3]};
+        if (!BF || p.y) put4(p.y + int64_t(m) * p.ldy, n, p.N, v, wide);
+        if constexpr (BF) put4(p.ybf + int64_t(m) * p.ldyb, n, p.N, v, p.away, wide_b);
+    };
+    auto value = [&](int mt, int t) {
+        return f32x4{float(acc[mt][t][0]), float(acc[mt][t][1]), float(acc[mt][t][2]), float(acc[mt][t][3])};
+    };
     if (p.ks == 1) {
 #pragma unroll
         for (int mt = 0; mt < MTILES; ++mt)
 #pragma unroll
             for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int m = m0 + 16 * mt + 4 * g + i, n = n0 + 16 * (2 * wave + t) + j;
-                    if (m < p.M && n < p.N) put_y<BF>(p, m, n, acc[mt][t][i]);
-                }
+                if (16 * mt + j < mrows) put(m0 + 16 * mt + j, n0 + 16 * (2 * wave + t) + 4 * g, value(mt, t));
         return;
     }
+    // the slice's real rows, 16 bytes a store, at device scope: piece o of a slice is columns
+    // 4 (o % kQuads) .. + 3 of row o / kQuads
+    constexpr int kQuads = kMfmaPanelCols / 4, kSlicePieces = MT * kQuads;
+    const __amdgpu_buffer_rsrc_t pr = make_rsrc(p.part + pbase, uint32_t(p.ks) * kSlicePieces * 16u);
 #pragma unroll
     for (int mt = 0; mt < MTILES; ++mt)
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int r = 16 * mt + 4 * g + i, c = 16 * (2 * wave + t) + j;
-                __hip_atomic_store(p.part + pbase + int64_t(slice) * (MT * kMfmaPanelCols) + r * kMfmaPanelCols + c,
-                                   acc[mt][t][i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+        for (int t = 0; t < 2; ++t) {
+            const int o = (16 * mt + j) * kQuads + 4 * (2 * wave + t) + g;
+            if (16 * mt + j < mrows)
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, value(mt, t)), pr,
+                                                       uint32_t(slice * kSlicePieces + o) * 16u, 0, kDevice);
+        }
     // same hand-off as the GEMV: completed device-scope stores, one ticket, ordered gather
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
@@ -238,36 +258,39 @@ __global__ __launch_bounds__(kThreads) void mfma_gemv_kernel(const MParams p) {
     }
     __syncthreads();
     if (!s_last) return;
-    // every output of the panel sums its slices in slice order; the loads of PER outputs x QB
-    // slices are all in flight before any is added
-    constexpr int PER = MT * kMfmaPanelCols / kThreads;   // outputs per thread (8 or 16)
-    constexpr int QB = 64 / PER;                            // slices per batch
-    float sum[PER];
+    // every piece of the panel sums its slices in slice order in fp64; the loads of PER pieces x QB
+    // slices are all in flight before any is added (rows past M load nothing)
+    constexpr int PER = kSlicePieces / kThreads;            // pieces per thread (2 or 4)
+    constexpr int QB = 32 / PER;                            // slices per batch
+    const int n_out = mrows * kQuads;
+    double sum[PER][4];
 #pragma unroll
-    for (int r = 0; r < PER; ++r) sum[r] = 0.f;
+    for (int r = 0; r < PER; ++r)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum[r][i] = 0.0;
     for (int q0 = 0; q0 < p.ks; q0 += QB) {
-        float v[PER][QB];
+        f32x4 v[PER][QB];
 #pragma unroll
         for (int r = 0; r < PER; ++r)
 #pragma unroll
             for (int u = 0; u < QB; ++u) {
                 const int o = tid + r * kThreads;
-                v[r][u] = (q0 + u < p.ks)
-                              ? __hip_atomic_load(p.part + pbase + int64_t(q0 + u) * (MT * kMfmaPanelCols) + o,
-                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                              : 0.f;
+                const uint32_t off = (o < n_out && q0 + u < p.ks) ? uint32_t((q0 + u) * kSlicePieces + o) * 16u : kOutOfRange;
+                v[r][u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(pr, off, 0, kDevice));
             }
 #pragma unroll
         for (int r = 0; r < PER; ++r)
 #pragma unroll
             for (int u = 0; u < QB; ++u)
-                if (q0 + u < p.ks) sum[r] += v[r][u];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) sum[r][i] += double(v[r][u][i]);
     }
 #pragma unroll
     for (int r = 0; r < PER; ++r) {
         const int o = tid + r * kThreads;
-        const int m = m0 + o / kMfmaPanelCols, n = n0 + o % kMfmaPanelCols;
-        if (m < p.M && n < p.N) put_y<BF>(p, m, n, sum[r]);
+        if (o < n_out)
+            put(m0 + o / kQuads, n0 + 4 * (o % kQuads),
+                f32x4{float(sum[r][0]), float(sum[r][1]), float(sum[r][2]), float(sum[r][3])});
     }
 }
 

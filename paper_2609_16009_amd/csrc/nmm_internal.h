@@ -37,7 +37,8 @@ constexpr int64_t kTicketBytes = kMaxTickets * 4;
 constexpr int kMfmaPanelCols = 128;
 constexpr int kMfmaStageRows = 64;
 constexpr int kHeadsCols = 64;             // columns per workgroup of the batched matrix-core kernel
-constexpr int kMfmaTargetGrid = 256;      // the matrix-core plan splits K until about this many workgroups
+constexpr int kMfmaTargetGrid = 256;      // the matrix-core plan splits K while the grid stays within this
+constexpr int64_t kMfmaShortK = 3072;
 constexpr int64_t kMfmaLongK = 2048;
 constexpr int kMfmaMinMDefault = 3;        // AUTO uses the matrix cores from this many rows on
 

@@ -98,9 +98,11 @@ nmm_status validate_gemv(const GemvArgs& a, int path) {
 }
 
 // The matrix-core partition: 128-column panels, K-slices of whole 64-row stages, x tiles of
-// 16 or 32 rows.  Splits are added only until the grid reaches about 256 workgroups: every
-// workgroup pays a fixed start-up latency and split-K tail, so one round of long streams beats
-// more, shorter ones (measured on the W_UQ, W_O and down shapes).
+// 16 or 32 rows.  As many slices as keep the grid within one workgroup per CU: a part-filled second
+// round costs more than shorter slices save (measured on MI355X at 4 / 32 rows, floor(256 / panels)
+// slices against the power of two nearest it: [4096, 5120] 6 slices 11.4 / 13.4 us against 8 13.7 /
+// 18.0, [1024, 2560] 12 slices 6.7 / 9.0 against 16 8.2 / 14.9, [4096, 8960] 3 slices 16.2 / 18.8
+// against 4 20.1 / 24.1; where the two agree, W_O's 4 and [8192, 8192]'s, nothing changes).
 nmm_status plan_mfma(int64_t M, int64_t K, int64_t N, GemvPlan* p) {
     GemvPlan q;
     q.path = NMM_PATH_MFMA;
@@ -115,10 +117,13 @@ nmm_status plan_mfma(int64_t M, int64_t K, int64_t N, GemvPlan* p) {
     }
     const int64_t panels = int64_t(q.mblocks) * q.n_full;
     const int64_t want = tuned("NMM_GEMV_TARGET", kMfmaTargetGrid);
-    const int64_t ks_cap = tuned("NMM_GEMV_MAXSPLIT", 16);
-    int64_t ks_want = 1;
-    const double ratio = double(want) / double(panels);
-    while (ks_want < ks_cap && double(ks_want) * 1.41421356 < ratio) ks_want *= 2;
+    // a short K takes at most 8 slices ([1536, 1536] 6.6 us, 12 slices 6.8; [512, 512] 5.1, 2 slices 6.3)
+    const int64_t ks_cap = tuned("NMM_GEMV_MAXSPLIT", K < kMfmaShortK ? 8 : 16);
+    int64_t ks_want = std::max<int64_t>(1, want / panels);
+    // fewer than 70 % of the CUs in use on a long K: two workgroups per CU, which still fit side by side
+    // ([4096, 16640], 130 panels: 28.3 us with 3 slices against 33.8 with one; on K = 1024 11.3 against 10.1)
+    if (ks_want * panels * 10 < want * 7 && K >= kMfmaLongK) ks_want = std::max(ks_want, 2 * want / panels);
+    ks_want = std::min(ks_want, ks_cap);
     int64_t r = rup(cdiv(K, ks_want), kMfmaStageRows);
     int64_t k = cdiv(K, r);
     if (panels > kMaxTickets) {

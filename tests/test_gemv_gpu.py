@@ -360,6 +360,23 @@ def test_batched_matrix_cores_agree_with_the_stream(K):
 
 # ------------------------------------------------------------------ matrix-core path
 
+@pytest.mark.parametrize("M", [3, 15, 16, 17, 31, 33])
+@pytest.mark.parametrize("K,N", [(512, 512), (1024, 2560), (4096, 5003), (2049, 16700)])
+def test_mfma_slices_integer_exact(M, K, N):
+    # slice counts that are no power of two, the gather of the real rows of a 16- or 32-row tile, and
+    # output rows on and off 16 bytes
+    c = syn.gemv_case(M + K % 89, M, K, N, syn.BF16, integer=True, ldx=(K + 7) // 8 * 8, ldw=(N + 7) // 8 * 8)
+    y_ref, a_ref = oracle.gemv(c.x, c.W, c.dt, K=K, N=N)
+    x, W = dev16(c.x, c.dt), dev16(c.W, c.dt)
+    for ldy in ((N + 3) // 4 * 4 + 4, N + 1):
+        y = torch.full((M, ldy), float("nan"), dtype=torch.float32, device="cuda")
+        nmm.nmm_gemv(x, W, y, N=N)
+        torch.cuda.synchronize()
+        assert_parity(y[:, :N], y_ref, a_ref, integer=True, what=f"slices {M}x{K}x{N}")
+        if ldy > N:
+            assert torch.isnan(y[:, N:]).all(), "columns past N were written"
+
+
 @pytest.mark.parametrize("M", [1, 2, 3, 4, 5, 8, 16, 17, 32])
 def test_uq_sweep_mfma_path(M):
     check_case(syn.uq_sweep(min(M, 32)) if M <= 32 else None, path=nmm.NMM_PATH_MFMA)
