@@ -152,26 +152,31 @@ def _check(status: int, where: str) -> None:
         raise NmmError(status, where)
 
 
+_CODES = {torch.bfloat16: NMM_BF16, torch.float16: NMM_F16}
+
+
 def _dtype_code(t: torch.Tensor, dt: int | None) -> int:
-    if t.dtype == torch.bfloat16:
-        return NMM_BF16
-    if t.dtype == torch.float16:
-        return NMM_F16
+    code = _CODES.get(t.dtype)
+    if code is not None:
+        return code
     if t.dtype in (torch.int16, torch.uint16) and dt in (NMM_F16, NMM_BF16):
         return dt
     raise TypeError("x and W must be bfloat16/float16 tensors, or int16 bit patterns with dt given")
 
 
 def _stream(stream) -> int:
+    """The handle of `stream` (None: the current device's current stream).  The current one is read as
+    a raw handle: building torch's Stream object for it takes 2.7 us, a third of a small call."""
     if stream is None:
-        stream = torch.cuda.current_stream()
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _ld(t: torch.Tensor) -> int:
-    if t.stride(-1) != 1:
+    s = t.stride()
+    if s[-1] != 1:
         raise ValueError("the last dimension must be contiguous")
-    return t.stride(-2) if t.dim() >= 2 else t.shape[-1]
+    return s[-2] if len(s) >= 2 else t.shape[-1]
 
 
 class Workspace:
@@ -185,6 +190,7 @@ class Workspace:
     def __init__(self, device=None):
         self.device = torch.device("cuda", torch.cuda.current_device()) if device is None else torch.device(device)
         self.buf = None
+        self.held = (0, 0)               # (pointer, bytes) of buf, replaced as one
         self._retired = []
 
     def get(self, nbytes: int, stream=None) -> tuple[int, int]:
@@ -199,7 +205,8 @@ class Workspace:
             if self.buf is not None:
                 self._retired.append(self.buf)
             self.buf = buf
-        return self.buf.data_ptr(), self.buf.numel()
+            self.held = (buf.data_ptr(), size)
+        return self.held
 
 
 def _torch_stream(stream, device) -> torch.cuda.Stream:
@@ -213,18 +220,38 @@ def _torch_stream(stream, device) -> torch.cuda.Stream:
 _default_ws: dict = {}
 
 
-def _workspace(ws, nbytes: int, device, stream=None) -> tuple[int, int]:
+def _workspace_of(ws, device, handle: int):
     """The workspace of one call.  Without one given, each (device, stream) pair has its own, so
     calls on different streams never share partial sums or counters."""
     if ws is None:
-        dev = torch.device(device)
-        key = (dev.index, _stream(stream))
+        key = (device.index, handle)
         ws = _default_ws.get(key)
         if ws is None:
-            ws = _default_ws[key] = Workspace(dev)
+            ws = _default_ws[key] = Workspace(device)
+    return ws
+
+
+def _workspace(ws, nbytes: int, device, stream=None) -> tuple[int, int]:
+    ws = _workspace_of(ws, torch.device(device), _stream(stream) if ws is None else 0)
     if isinstance(ws, Workspace):
         return ws.get(nbytes, stream)
     return ws.data_ptr(), ws.numel() * ws.element_size()
+
+
+def _call(fn, where: str, size, args: tuple, ws, device, stream) -> None:
+    """fn(*args, workspace, bytes, stream) on the workspace as it stands.  A call whose workspace is too
+    small is refused before it enqueues anything; only then is the size asked for (``size()``) and the
+    workspace grown, so that a call whose workspace fits plans once."""
+    handle = _stream(stream)
+    w = _workspace_of(ws, device, handle)
+    if isinstance(w, Workspace):
+        status = fn(*args, *w.held, handle)
+        if status == NMM_ERR_WORKSPACE:
+            status = fn(*args, *w.get(size(), stream), handle)
+    else:
+        status = fn(*args, w.data_ptr(), w.numel() * w.element_size(), handle)
+    if status != NMM_OK:
+        raise NmmError(status, where)
 
 
 def _prepared_workspace(ws, nbytes: int, device):
@@ -243,10 +270,10 @@ def nmm_gemv(x: torch.Tensor, W: torch.Tensor, y: torch.Tensor, *, N: int | None
     code = _dtype_code(x, dt)
     M, K = x.shape[0], W.shape[0]
     N = W.shape[1] if N is None else N
-    need = lib().nmm_gemv_workspace_size(M, K, N, code, path)
-    wp, wb = _workspace(workspace, need, x.device, stream)
-    _check(lib().nmm_gemv(M, K, N, code, x.data_ptr(), _ld(x), W.data_ptr(), _ld(W), y.data_ptr(),
-                          _ld(y), path, wp, wb, _stream(stream)), "nmm_gemv")
+    L = lib()
+    _call(L.nmm_gemv, "nmm_gemv", lambda: L.nmm_gemv_workspace_size(M, K, N, code, path),
+          (M, K, N, code, x.data_ptr(), _ld(x), W.data_ptr(), _ld(W), y.data_ptr(), _ld(y), path), workspace, x.device,
+          stream)
     return y
 
 
@@ -268,11 +295,10 @@ def nmm_gemv_bf16(x: torch.Tensor, W: torch.Tensor, y_bf16: torch.Tensor, *, rou
     code = _dtype_code(x, dt)
     M, K = x.shape[0], W.shape[0]
     N = W.shape[1] if N is None else N
-    need = lib().nmm_gemv_workspace_size(M, K, N, code, path)
-    wp, wb = _workspace(workspace, need, x.device, stream)
-    _check(lib().nmm_gemv_bf16(M, K, N, code, x.data_ptr(), _ld(x), W.data_ptr(), _ld(W), y_bf16.data_ptr(),
-                               _ld(y_bf16), round, y.data_ptr() if y is not None else None,
-                               _ld(y) if y is not None else 0, path, wp, wb, _stream(stream)), "nmm_gemv_bf16")
+    L = lib()
+    _call(L.nmm_gemv_bf16, "nmm_gemv_bf16", lambda: L.nmm_gemv_workspace_size(M, K, N, code, path),
+          (M, K, N, code, x.data_ptr(), _ld(x), W.data_ptr(), _ld(W), y_bf16.data_ptr(), _ld(y_bf16), round,
+           y.data_ptr() if y is not None else None, _ld(y) if y is not None else 0, path), workspace, x.device, stream)
     return y_bf16
 
 
@@ -283,13 +309,12 @@ def nmm_batched_gemv_bf16(x: torch.Tensor, W: torch.Tensor, y_bf16: torch.Tensor
     code = _dtype_code(x, dt)
     B, M, K = x.shape[0], x.shape[1], W.shape[1]
     N = W.shape[2] if N is None else N
-    need = lib().nmm_batched_gemv_workspace_size(B, M, K, N, code, path)
-    wp, wb = _workspace(workspace, need, x.device, stream)
-    _check(lib().nmm_batched_gemv_bf16(B, M, K, N, code, x.data_ptr(), _ld(x), x.stride(0), W.data_ptr(), _ld(W),
-                                       W.stride(0), y_bf16.data_ptr(), _ld(y_bf16), y_bf16.stride(0), round,
-                                       y.data_ptr() if y is not None else None, _ld(y) if y is not None else 0,
-                                       y.stride(0) if y is not None else 0, path, wp, wb, _stream(stream)),
-           "nmm_batched_gemv_bf16")
+    L = lib()
+    _call(L.nmm_batched_gemv_bf16, "nmm_batched_gemv_bf16",
+          lambda: L.nmm_batched_gemv_workspace_size(B, M, K, N, code, path),
+          (B, M, K, N, code, x.data_ptr(), _ld(x), x.stride(0), W.data_ptr(), _ld(W), W.stride(0), y_bf16.data_ptr(),
+           _ld(y_bf16), y_bf16.stride(0), round, y.data_ptr() if y is not None else None,
+           _ld(y) if y is not None else 0, y.stride(0) if y is not None else 0, path), workspace, x.device, stream)
     return y_bf16
 
 
@@ -298,11 +323,10 @@ def nmm_mla_query(q: torch.Tensor, q_bf16: torch.Tensor, w_uk: torch.Tensor, qla
     """q_out[h] = bf16([q_nope[h] . W_UK[h] | RoPE(q[h, nope:], position)]) for q [heads, nope + rope] fp32,
     q_bf16 its bf16 rounding, w_uk [heads, nope, kv_lora]; qlat [heads, kv_lora] fp32 receives the products."""
     heads, kv_lora = w_uk.shape[0], w_uk.shape[2]
-    need = lib().nmm_mla_query_workspace_size(heads, nope, kv_lora)
-    wp, wb = _workspace(workspace, need, q.device, stream)
-    _check(lib().nmm_mla_query(heads, nope, rope, kv_lora, q.data_ptr(), q_bf16.data_ptr(), w_uk.data_ptr(),
-                               int(position), float(theta), qlat.data_ptr(), q_out.data_ptr(), _ld(q_out), wp, wb,
-                               _stream(stream)), "nmm_mla_query")
+    L = lib()
+    _call(L.nmm_mla_query, "nmm_mla_query", lambda: L.nmm_mla_query_workspace_size(heads, nope, kv_lora),
+          (heads, nope, rope, kv_lora, q.data_ptr(), q_bf16.data_ptr(), w_uk.data_ptr(), int(position), float(theta),
+           qlat.data_ptr(), q_out.data_ptr(), _ld(q_out)), workspace, q.device, stream)
     return q_out
 
 
@@ -338,10 +362,10 @@ def nmm_gemv_nt(x: torch.Tensor, Wt: torch.Tensor, y: torch.Tensor, *, K: int | 
     code = _dtype_code(x, dt)
     M, N = x.shape[0], Wt.shape[0]
     K = Wt.shape[1] if K is None else K
-    need = lib().nmm_gemv_nt_workspace_size(M, K, N, code)
-    wp, wb = _workspace(workspace, need, x.device, stream)
-    _check(lib().nmm_gemv_nt(M, K, N, code, x.data_ptr(), _ld(x), Wt.data_ptr(), _ld(Wt), y.data_ptr(), _ld(y),
-                             wp, wb, _stream(stream)), "nmm_gemv_nt")
+    L = lib()
+    _call(L.nmm_gemv_nt, "nmm_gemv_nt", lambda: L.nmm_gemv_nt_workspace_size(M, K, N, code),
+          (M, K, N, code, x.data_ptr(), _ld(x), Wt.data_ptr(), _ld(Wt), y.data_ptr(), _ld(y)), workspace, x.device,
+          stream)
     return y
 
 
@@ -366,9 +390,9 @@ def nmm_mla_kv_update(h: torch.Tensor, w: torch.Tensor, gamma: torch.Tensor, mm:
     """MatMul 2 (h . w -> mm fp32) and the cache entry cache[position] = bf16([RMSNorm | RoPE])."""
     k = _kv_struct(h, w, gamma, mm, cache, kv_lora=kv_lora, rope=rope, eps=eps, theta=theta,
                    position=position, round=round)
-    need = lib().nmm_mla_kv_update_workspace_size(ctypes.byref(k))
-    wp, wb = _workspace(workspace, need, h.device, stream)
-    _check(lib().nmm_mla_kv_update(ctypes.byref(k), wp, wb, _stream(stream)), "nmm_mla_kv_update")
+    L, ref = lib(), ctypes.byref(k)
+    _call(L.nmm_mla_kv_update, "nmm_mla_kv_update", lambda: L.nmm_mla_kv_update_workspace_size(ref), (ref,), workspace,
+          h.device, stream)
 
 
 def nmm_batched_gemv(x: torch.Tensor, W: torch.Tensor, y: torch.Tensor, *, N: int | None = None,
@@ -378,11 +402,10 @@ def nmm_batched_gemv(x: torch.Tensor, W: torch.Tensor, y: torch.Tensor, *, N: in
     code = _dtype_code(x, dt)
     B, M, K = x.shape[0], x.shape[1], W.shape[1]
     N = W.shape[2] if N is None else N
-    need = lib().nmm_batched_gemv_workspace_size(B, M, K, N, code, path)
-    wp, wb = _workspace(workspace, need, x.device, stream)
-    _check(lib().nmm_batched_gemv(B, M, K, N, code, x.data_ptr(), _ld(x), x.stride(0), W.data_ptr(),
-                                  _ld(W), W.stride(0), y.data_ptr(), _ld(y), y.stride(0), path, wp,
-                                  wb, _stream(stream)), "nmm_batched_gemv")
+    L = lib()
+    _call(L.nmm_batched_gemv, "nmm_batched_gemv", lambda: L.nmm_batched_gemv_workspace_size(B, M, K, N, code, path),
+          (B, M, K, N, code, x.data_ptr(), _ld(x), x.stride(0), W.data_ptr(), _ld(W), W.stride(0), y.data_ptr(), _ld(y),
+           y.stride(0), path), workspace, x.device, stream)
     return y
 
 
@@ -527,9 +550,9 @@ def nmm_mla_decode_chain(dims: dict, bufs: dict, *, workspace=None, stream=None,
     ``events`` is an optional list of >= 6 torch.cuda.Event(enable_timing=True); ``kv`` the
     optional cache entry (see _chain_struct)."""
     c, keep = _chain_struct(dims, bufs, events, kv)
-    need = lib().nmm_mla_decode_chain_workspace_size(ctypes.byref(c))
-    wp, wb = _workspace(workspace, need, bufs["x"].device, stream)
-    _check(lib().nmm_mla_decode_chain(ctypes.byref(c), wp, wb, _stream(stream)), "nmm_mla_decode_chain")
+    L, ref = lib(), ctypes.byref(c)
+    _call(L.nmm_mla_decode_chain, "nmm_mla_decode_chain", lambda: L.nmm_mla_decode_chain_workspace_size(ref), (ref,),
+          workspace, bufs["x"].device, stream)
     del keep
 
 
@@ -542,11 +565,11 @@ def nmm_latent_attention(q: torch.Tensor, kv: torch.Tensor, out: torch.Tensor, s
     """out[h, :d_v] = softmax(scale * q[h] . kv[:, :d_qk]^T) . kv[:, :d_v]  (bf16 in, fp32 out)."""
     heads, seq = q.shape[0], kv.shape[0]
     d_qk = q.shape[1] if d_qk is None else d_qk
-    need = lib().nmm_latent_attention_workspace_size(heads, seq, d_qk, d_v)
-    wp, wb = _workspace(workspace, need, q.device, stream)
-    _check(lib().nmm_latent_attention(heads, seq, d_qk, d_v, q.data_ptr(), _ld(q), kv.data_ptr(),
-                                      _ld(kv), float(scale), out.data_ptr(), _ld(out), wp, wb,
-                                      _stream(stream)), "nmm_latent_attention")
+    L = lib()
+    _call(L.nmm_latent_attention, "nmm_latent_attention",
+          lambda: L.nmm_latent_attention_workspace_size(heads, seq, d_qk, d_v),
+          (heads, seq, d_qk, d_v, q.data_ptr(), _ld(q), kv.data_ptr(), _ld(kv), float(scale), out.data_ptr(), _ld(out)),
+          workspace, q.device, stream)
     return out
 
 
@@ -556,11 +579,11 @@ def nmm_latent_attention_bf16(q: torch.Tensor, kv: torch.Tensor, out: torch.Tens
     """nmm_latent_attention, also writing out_bf16 = bf16(out)."""
     heads, seq = q.shape[0], kv.shape[0]
     d_qk = q.shape[1] if d_qk is None else d_qk
-    need = lib().nmm_latent_attention_workspace_size(heads, seq, d_qk, d_v)
-    wp, wb = _workspace(workspace, need, q.device, stream)
-    _check(lib().nmm_latent_attention_bf16(heads, seq, d_qk, d_v, q.data_ptr(), _ld(q), kv.data_ptr(), _ld(kv),
-                                           float(scale), out.data_ptr(), _ld(out), out_bf16.data_ptr(), _ld(out_bf16),
-                                           wp, wb, _stream(stream)), "nmm_latent_attention_bf16")
+    L = lib()
+    _call(L.nmm_latent_attention_bf16, "nmm_latent_attention_bf16",
+          lambda: L.nmm_latent_attention_workspace_size(heads, seq, d_qk, d_v),
+          (heads, seq, d_qk, d_v, q.data_ptr(), _ld(q), kv.data_ptr(), _ld(kv), float(scale), out.data_ptr(), _ld(out),
+           out_bf16.data_ptr(), _ld(out_bf16)), workspace, q.device, stream)
     return out
 
 
@@ -571,13 +594,12 @@ def nmm_latent_attention_ex(q: torch.Tensor, kv: torch.Tensor, out: torch.Tensor
     of the output."""
     heads, seq = q.shape[0], kv.shape[0]
     d_qk = q.shape[1] if d_qk is None else d_qk
-    need = lib().nmm_latent_attention_ex_workspace_size(heads, seq, d_qk, d_v, splits)
-    wp, wb = _workspace(workspace, need, q.device, stream)
-    _check(lib().nmm_latent_attention_ex(heads, seq, d_qk, d_v, q.data_ptr(), _ld(q), kv.data_ptr(), _ld(kv),
-                                         float(scale), out.data_ptr(), _ld(out),
-                                         out_bf16.data_ptr() if out_bf16 is not None else None,
-                                         _ld(out_bf16) if out_bf16 is not None else 0, int(splits), wp, wb,
-                                         _stream(stream)), "nmm_latent_attention_ex")
+    L = lib()
+    _call(L.nmm_latent_attention_ex, "nmm_latent_attention_ex",
+          lambda: L.nmm_latent_attention_ex_workspace_size(heads, seq, d_qk, d_v, splits),
+          (heads, seq, d_qk, d_v, q.data_ptr(), _ld(q), kv.data_ptr(), _ld(kv), float(scale), out.data_ptr(), _ld(out),
+           out_bf16.data_ptr() if out_bf16 is not None else None, _ld(out_bf16) if out_bf16 is not None else 0,
+           int(splits)), workspace, q.device, stream)
     return out
 
 

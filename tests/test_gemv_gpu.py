@@ -247,6 +247,29 @@ def test_infinity_propagates_to_its_column_only():
     assert np.isfinite(y[mask]).all()
 
 
+def test_a_workspace_grows_when_a_call_asks_and_a_given_buffer_does_not():
+    # the call is tried on the workspace as it stands: a fresh or outgrown Workspace is grown and the call
+    # repeated, on the caller's stream; a tensor that is too small stays refused, with y untouched
+    s = torch.cuda.Stream()
+    ws = nmm.Workspace()
+    for M, K, N in ((1, 7168, 576), (4, 7168, 2112), (1, 512, 512), (16, 16384, 7168)):
+        c = syn.gemv_case(40 + M, M, K, N, syn.BF16, integer=True)
+        x, W = dev16(c.x, c.dt), dev16(c.W, c.dt)
+        y = torch.zeros((M, N), device="cuda")
+        torch.cuda.synchronize()
+        need = nmm.nmm_gemv_workspace_size(M, K, N)
+        nmm.nmm_gemv(x, W, y, workspace=ws, stream=s)
+        s.synchronize()
+        y_ref, a_ref = oracle.gemv(c.x, c.W, c.dt)
+        assert_parity(y, y_ref, a_ref, integer=True)
+        assert need == 0 or ws.buf.numel() >= need and ws.held == (ws.buf.data_ptr(), ws.buf.numel())
+        if need:
+            with pytest.raises(nmm.NmmError) as e:
+                nmm.nmm_gemv(x, W, y.zero_(), workspace=torch.zeros(need // 2, dtype=torch.uint8, device="cuda"))
+            torch.cuda.synchronize()
+            assert e.value.status == nmm.NMM_ERR_WORKSPACE and not y.any()
+
+
 # ------------------------------------------------------------------ batched (per-head)
 
 def test_absorbed_heads_two_steps():
