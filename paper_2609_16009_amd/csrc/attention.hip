@@ -26,6 +26,8 @@
 //    At 576 / 512, while the grid fits one workgroup per CU, four or two workgroups share each
 //    (head block, span), each taking its share of the column tiles (all compute the scores):
 //    more workgroups, each with a share of the P.V work and the stores.
+//  * Long spans (eight chunks and more) also touch the chunk after next, the span's workgroups a share
+//    of its lines each, so that its rows wait in the XCD's L2 when their staging starts.
 //  * Spans write (reference, sum, unnormalised output) partials; a merge kernel on the same
 //    stream combines them in span order.  The head blocks of one span run on one XCD (workgroup
 //    ids 8 apart), so its L2 reads the span's cache rows from HBM once for all of them.
@@ -57,17 +59,20 @@ constexpr int kDefaultMaxChunks = 8;      // or more spans, so that a span has a
 constexpr int kDefaultFitChunks = 4;      // or this many while one workgroup per 16-head block and span fits the CUs,
 constexpr int kDefaultMinChunks = 2;      // but spans of at least this many chunks (one-chunk spans merge
                                           // more partials than their parallelism saves)
+constexpr int kTouchMinChunks = 8;        // spans of this many chunks touch the chunk kTouchAhead ahead
+constexpr int kTouchAhead = 2;
 constexpr int kComputeUnits = 256;        // MI355X; an attention workgroup holds a CU (its LDS)
 
 // Attention launch workgroups of HT head tiles, each taking 4 NTW of d_v's 16-column tiles (of
 // VS column parts).
-template <int HT, int NTW, bool EXACT, int VS>
+template <int HT, int NTW, bool EXACT, int VS, bool TOUCH>
 __global__ __launch_bounds__(kAThreads) void attention_kernel(const AttnParams p) {
-    attention_block<HT, kMaxKs, NTW, EXACT, VS>(p, blockIdx.x);
+    attention_block<HT, kMaxKs, NTW, EXACT, VS, TOUCH>(p, blockIdx.x);
 }
 
+template <int BATCH>
 __global__ __launch_bounds__(kMergeWideThreads) void attention_merge_kernel(const AttnParams p) {
-    merge_block_wide(p, static_cast<int>(blockIdx.x));
+    merge_block_wide<BATCH>(p, static_cast<int>(blockIdx.x));
 }
 
 struct AttnPlan {
@@ -137,17 +142,17 @@ nmm_status plan_attention(int64_t heads, int64_t seq, int64_t dqk, int64_t dv, A
     return NMM_OK;
 }
 
-template <bool EXACT>
+template <bool EXACT, bool TOUCH>
 nmm_status launch_attention(const AttnParams& p, int64_t grid, int vsplit, hipStream_t s) {
     const dim3 g(static_cast<uint32_t>(grid));
     if (vsplit == 4)
-        hipLaunchKernelGGL((attention_kernel<1, kMaxNtw / 4, true, 4>), g, dim3(kAThreads), 0, s, p);
+        hipLaunchKernelGGL((attention_kernel<1, kMaxNtw / 4, true, 4, TOUCH>), g, dim3(kAThreads), 0, s, p);
     else if (vsplit == 2)
-        hipLaunchKernelGGL((attention_kernel<1, kMaxNtw / 2, true, 2>), g, dim3(kAThreads), 0, s, p);
+        hipLaunchKernelGGL((attention_kernel<1, kMaxNtw / 2, true, 2, TOUCH>), g, dim3(kAThreads), 0, s, p);
     else if (p.hbh == kAloneHeads)
-        hipLaunchKernelGGL((attention_kernel<1, kMaxNtw, EXACT, 1>), g, dim3(kAThreads), 0, s, p);
+        hipLaunchKernelGGL((attention_kernel<1, kMaxNtw, EXACT, 1, TOUCH>), g, dim3(kAThreads), 0, s, p);
     else
-        hipLaunchKernelGGL((attention_kernel<kHt, kMaxNtw, EXACT, 1>), g, dim3(kAThreads), 0, s, p);
+        hipLaunchKernelGGL((attention_kernel<kHt, kMaxNtw, EXACT, 1, TOUCH>), g, dim3(kAThreads), 0, s, p);
     return hipGetLastError() == hipSuccess ? NMM_OK : NMM_ERR_HIP;
 }
 
@@ -218,6 +223,12 @@ nmm_status prepare(int64_t heads, int64_t seq, int64_t d_qk, int64_t d_v, const 
     p.n_hb = a.n_hb;
     p.hbh = a.hbh;
     p.xcd_map = a.xcd_map;
+    // Spans of many chunks: the workgroups of a span bring the chunk two ahead into L2, which the double
+    // buffer alone (one chunk per span in flight, 4.7 MB over 64 spans) cannot cover from HBM: 8 heads x
+    // 131072 positions 70.1 -> 56.7 us, 128 x 65536 cold 46.2 -> 41.3, 128 x 32768 cold 29.7 -> 27.4; level
+    // with the cache in the MALL.  Short spans gain nothing (four chunks: 13.0 either way), and beside a
+    // GEMV's stream the attention keeps its loads as they are.
+    p.touch = hbh == kAloneHeads && a.span >= kTouchMinChunks * kCh ? kTouchAhead : 0;
     p.scale_log2 = scale * 1.4426950408889634f;
     p.kv_extent = static_cast<uint32_t>(extent);
     p.q_extent = static_cast<uint32_t>(q_extent);
@@ -245,15 +256,20 @@ namespace nmm {
 nmm_status launch_attention_merge(const AttnLaunch& l, hipStream_t s) {
     if (l.merge_grid == 0) return NMM_OK;
     static_assert(4 * kMergeWideThreads == kMergeThreads, "the two merge forms cut a head's columns alike");
-    hipLaunchKernelGGL(attention_merge_kernel, dim3(static_cast<uint32_t>(l.merge_grid)), dim3(kMergeWideThreads), 0,
-                       s, l.p);
+    const dim3 grid(static_cast<uint32_t>(l.merge_grid)), block(kMergeWideThreads);
+    // every span's loads in one batch: with batches of 16, 64 heads x 64 spans took 20.5 us with the
+    // attention where 64 at once takes 17.3, 16 heads x 33 spans 11.8 and 10.1
+    if (l.p.nsp > 32) hipLaunchKernelGGL(attention_merge_kernel<64>, grid, block, 0, s, l.p);
+    else if (l.p.nsp > 16) hipLaunchKernelGGL(attention_merge_kernel<32>, grid, block, 0, s, l.p);
+    else hipLaunchKernelGGL(attention_merge_kernel<16>, grid, block, 0, s, l.p);
     return hipGetLastError() == hipSuccess ? NMM_OK : NMM_ERR_HIP;
 }
 
 nmm_status launch_attention_kernel(const AttnLaunch& l, hipStream_t s) {
     if (l.grid == 0) return NMM_OK;
-    return l.variant == kAttnExact ? launch_attention<true>(l.p, l.grid, l.vsplit, s)
-                                   : launch_attention<false>(l.p, l.grid, l.vsplit, s);
+    if (l.variant != kAttnExact) return launch_attention<false, false>(l.p, l.grid, l.vsplit, s);
+    return l.p.touch > 0 ? launch_attention<true, true>(l.p, l.grid, l.vsplit, s)
+                         : launch_attention<true, false>(l.p, l.grid, l.vsplit, s);
 }
 
 nmm_status launch_prepared_attention(const AttnLaunch& l, hipStream_t s) {

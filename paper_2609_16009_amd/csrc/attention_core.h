@@ -58,6 +58,7 @@ struct AttnParams {
     int nsp, span, n_hb;
     int hbh;            // heads per block (16 per head tile)
     int xcd_map;        // 1: the head blocks of a span grouped on one XCD (grid padded to 8 spans)
+    int touch;          // chunks ahead whose cache lines a span's workgroups bring into L2 (0: none)
     float scale_log2;   // scale * log2(e): scores are kept in log2 units
     uint32_t kv_extent; // bytes of the cache that may be read
     uint32_t q_extent;  // bytes of q that may be read
@@ -161,6 +162,10 @@ __device__ __forceinline__ float* red_buffer() {
     __shared__ __attribute__((aligned(16))) float red[4 * kMaxHt * 16];
     return red;
 }
+__device__ __forceinline__ uint32_t* touch_sink() {
+    __shared__ __attribute__((aligned(16))) uint32_t sink[kAThreads];
+    return sink;
+}
 __device__ __forceinline__ int* flag_buffer() {
     __shared__ __attribute__((aligned(16))) int flags[8];
     return flags;
@@ -199,8 +204,8 @@ __device__ __forceinline__ bool block_of(const AttnParams& p, int bid, int nb, i
 //    (O^T = V^T . P^T, V^T fragments by ds_read_b64_tr_b16 from the same staged rows).
 //  * The result is stored straight from the accumulators, 64 contiguous bytes of 16 rows per store.
 // KS = d_qk / 32 and NTW = column tiles per position group are upper bounds; EXACT: the shape
-// matches them.
-template <int HT, int KS, int NTW, bool EXACT, int VS = 1>
+// matches them.  TOUCH (a kernel of its own, as its set-up costs a short span 0.25 us): see below.
+template <int HT, int KS, int NTW, bool EXACT, int VS = 1, bool TOUCH = false>
 __device__ __forceinline__ void attention_block(const AttnParams p, int bid) {
     constexpr int W = kAWaves;
     constexpr int HB = 16 * HT;
@@ -284,6 +289,22 @@ __device__ __forceinline__ void attention_block(const AttnParams p, int bid) {
     }
     const int a4 = j >> 2, b4 = j & 3;
 
+    static_assert(EXACT || !TOUCH, "touches know the 576-column rows");
+    // The span's workgroups share the touches of a chunk: 64-byte pieces u = tid + kAThreads i of this one's
+    // share, row u / pieces per row.
+    constexpr int kTouch = 2;                  // touches per wave and chunk
+    uint32_t toff[kTouch];
+    if constexpr (TOUCH) {
+        constexpr int kPieces = kMaxCols * 2 / 64;
+        const int nb = p.n_hb * VS, share = (kCh * kPieces + nb - 1) / nb;
+#pragma unroll
+        for (int i = 0; i < kTouch; ++i) {
+            const int v = tid + kAThreads * i, u = hbv * share + v;
+            const int row = u / kPieces, c = u - row * kPieces;
+            toff[i] = v < share && row < kCh ? uint32_t(row) * row_bytes + uint32_t(c) * 64u : kOutOfRange;
+        }
+    }
+
     auto chunk = [&](const uint16_t* cur, uint16_t* nxt, int ck) {
         const int c0 = s_begin + ck * kCh;
         // the next chunk streams into the other buffer while this one is computed (every wave
@@ -323,6 +344,18 @@ __device__ __forceinline__ void attention_block(const AttnParams p, int bid) {
 #pragma unroll
             for (int k = 0; k < Stage<W>::kIns; ++k)
                 if (k >= KS || (!EXACT && k >= ksteps)) stg.piece(nxt, kvr, k, spr, next_off, wave);
+        }
+
+        // bring a later chunk's lines into L2 (the values go to a sink nothing reads); these loads come
+        // after the staging's, so the wait at the chunk's end can leave them in flight
+        const bool touched = TOUCH && ck + p.touch < nchunks;
+        if (TOUCH && touched) {
+            uint32_t* const sink = touch_sink() + 64 * wave;
+#pragma unroll
+            for (int i = 0; i < kTouch; ++i)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                    kvr, (lds_void*)sink, 4, toff[i] == kOutOfRange ? kOutOfRange : toff[i] + uint32_t(c0 + p.touch * kCh) * row_bytes, 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
         }
 
         // ---- scores in log2 units (positions past the span masked) and this wave's maximum per
@@ -440,8 +473,13 @@ __device__ __forceinline__ void attention_block(const AttnParams p, int bid) {
 
         // ---- the next chunk must have landed (this wave's loads, then every wave's), and every
         // wave must be done with this chunk's rows and P
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
+        if (TOUCH && touched) {
+            wait_vm<kTouch>();
+            lds_sync();
+        } else {
+            __builtin_amdgcn_s_waitcnt(0);
+            __syncthreads();
+        }
     };
     for (int ck = 0; ck < nchunks; ck += 2) {
         chunk(kv_a, kv_b, ck);
@@ -508,9 +546,9 @@ __device__ __forceinline__ void attention_block(const AttnParams p, int bid) {
 // Merge the spans of each head in span order:
 //   out = sum_s w_s O_s / sum_s w_s l_s,  w_s = 2^(m_s - M),  M = max_s m_s.
 // Lane s of every wave loads span s's (m, l) (at most 64 spans), so M and the normaliser come from
-// one load and fixed-order butterflies; each thread loads its columns of every span at once and
-// sums them in span order with explicit fused multiply-adds, the weights taken from lane s.  A
-// block waits for about two memory round trips.  Two forms, which give the same bits (the same
+// one load and fixed-order butterflies; each thread loads its columns of every span at once (up to 64
+// in merge_block_wide, 32 in merge_block) and sums them in span order with explicit fused multiply-adds,
+// the weights taken from lane s.  A block waits for about one memory round trip.  Two forms, which give the same bits (the same
 // operations on every output, in the same order):
 //  * merge_block: block `blk` owns one head and 256 of its columns, one per thread `tid` (heads x
 //    ceil(d_v / 256) blocks of 256 threads): many light blocks, for the workgroups another
@@ -521,23 +559,69 @@ __device__ __forceinline__ void attention_block(const AttnParams p, int bid) {
 constexpr int kMergeThreads = 256;
 constexpr int kMergeBatch = 32;
 constexpr int kMergeWideThreads = 64;    // threads per block of merge_block_wide (256 columns)
-constexpr int kMergeWideBatch = 16;  // spans merge_block_wide loads at once
 
-// M's weight of this lane's span and the normaliser sum_s w_s l_s, the same in every lane
-__device__ __forceinline__ float2 merge_weights(const AttnParams& p, int64_t base, int lane) {
+// The butterflies of a wave: xor by 1 and 2 inside quads, then mirrors (every lane of a quad, then of
+// eight, holds the same value by then, so a mirror is an exchange by 4, then by 8), then rows.  DPP and
+// permlane exchanges: __shfl_xor's LDS round trips, twelve in a row, took longer than the merge's loads.
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, false));
+}
+constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kRowHalfMirror = 0x141, kRowMirror = 0x140;
+__device__ __forceinline__ float wave_max(float x) {
+    x = fmaxf(x, dpp<kQuadXor1>(x));
+    x = fmaxf(x, dpp<kQuadXor2>(x));
+    x = fmaxf(x, dpp<kRowHalfMirror>(x));
+    x = fmaxf(x, dpp<kRowMirror>(x));
+    const u32x2 a = swap16(__float_as_uint(x), __float_as_uint(x));
+    x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const u32x2 b = swap32(__float_as_uint(x), __float_as_uint(x));
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float wave_sum(float x) {
 #pragma clang fp contract(off)
-    float2 m_l = float2{-INFINITY, 0.f};
-    if (lane < p.nsp) m_l = *reinterpret_cast<const float2*>(p.part_ml + (base + int64_t(lane) * p.hbh) * 2);
-    float M = m_l.x;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) M = fmaxf(M, __shfl_xor(M, off));
-    const float w = (m_l.x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m_l.x - M);
-    float den = w * m_l.y;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) den += __shfl_xor(den, off);
-    return float2{w, den};
+    x = x + dpp<kQuadXor1>(x);
+    x = x + dpp<kQuadXor2>(x);
+    x = x + dpp<kRowHalfMirror>(x);
+    x = x + dpp<kRowMirror>(x);
+    const u32x2 a = swap16(__float_as_uint(x), __float_as_uint(x));
+    x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    const u32x2 b = swap32(__float_as_uint(x), __float_as_uint(x));
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
+// M's weight of this lane's span and the normaliser sum_s w_s l_s, the same in every lane
+__device__ __forceinline__ float2 merge_weights(const float2 m_l) {
+#pragma clang fp contract(off)
+    const float M = wave_max(m_l.x);
+    const float w = (m_l.x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m_l.x - M);
+    return float2{w, wave_sum(w * m_l.y)};
+}
+
+// The span partials of one head, from its first column: spans o_step bytes apart.  Loads are raw buffer
+// loads whose offset falls out of range past the last span or column, so a batch is straight-line code
+// (a branch per load kept the loads of a batch from going out together).
+struct MergeHead {
+    __amdgpu_buffer_rsrc_t rsrc;
+    uint32_t o_step;
+    float2 m_l;          // lane s: span s's reference and sum
+    __device__ __forceinline__ void init(const AttnParams& p, int h, int lane) {
+        const int hb = h / p.hbh, hl = h - hb * p.hbh;
+        const int64_t base = int64_t(hb) * p.nsp * p.hbh + hl;      // (block, span 0, head) row
+        o_step = uint32_t(p.hbh) * uint32_t(p.dv) * 4u;
+        rsrc = make_rsrc(p.part_o + base * p.dv, uint32_t(p.nsp - 1) * o_step + uint32_t(p.dv) * 4u);
+        m_l = float2{-INFINITY, 0.f};
+        if (lane < p.nsp) m_l = *reinterpret_cast<const float2*>(p.part_ml + (base + int64_t(lane) * p.hbh) * 2);
+    }
+    __device__ __forceinline__ uint32_t at(const AttnParams& p, int span, int c) const {
+        return span < p.nsp && c < p.dv ? uint32_t(span) * o_step + uint32_t(c) * 4u : kOutOfRange;
+    }
+};
+__device__ __forceinline__ float weight_of(float w, int span) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), span));
+}
+
+// Spans past the last have weight 0 and read 0: adding them leaves the sum as it is.
 __device__ __forceinline__ void merge_block(const AttnParams& p, int blk, int tid) {
     // no contraction of its own: every translation unit that inlines this rounds alike (the
     // products of the sum are explicit fused multiply-adds)
@@ -545,67 +629,60 @@ __device__ __forceinline__ void merge_block(const AttnParams& p, int blk, int ti
     const int n_cb = (p.dv + kMergeThreads - 1) / kMergeThreads;
     const int h = blk / n_cb, cb = blk - h * n_cb;
     const int n = cb * kMergeThreads + tid;
-    const int lane = tid & 63;
-    const int hb = h / p.hbh, hl = h - hb * p.hbh;
-    const int64_t base = int64_t(hb) * p.nsp * p.hbh + hl;      // (block, span 0, head) row
-    const float* src = p.part_o + base * p.dv + n;
-    const int64_t o_step = int64_t(p.hbh) * p.dv;
-    const bool active = n < p.dv;
+    MergeHead mh;
+    mh.init(p, h, tid & 63);
     // the partial outputs first (their loads are independent of the weights)
     float v[kMergeBatch];
 #pragma unroll
-    for (int u = 0; u < kMergeBatch; ++u) v[u] = (active && u < p.nsp) ? src[u * o_step] : 0.f;
-    const float2 wd = merge_weights(p, base, lane);
+    for (int u = 0; u < kMergeBatch; ++u)
+        v[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(mh.rsrc, mh.at(p, u, n), 0, 0));
+    const float2 wd = merge_weights(mh.m_l);
     float acc = 0.f;
     for (int s0 = 0; s0 < p.nsp; s0 += kMergeBatch) {
         if (s0 > 0) {
 #pragma unroll
-            for (int u = 0; u < kMergeBatch; ++u) v[u] = (active && s0 + u < p.nsp) ? src[(s0 + u) * o_step] : 0.f;
+            for (int u = 0; u < kMergeBatch; ++u)
+                v[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(mh.rsrc, mh.at(p, s0 + u, n), 0, 0));
         }
 #pragma unroll
-        for (int u = 0; u < kMergeBatch; ++u)
-            if (s0 + u < p.nsp) acc = __builtin_fmaf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(wd.x), s0 + u)), v[u], acc);
+        for (int u = 0; u < kMergeBatch; ++u) acc = __builtin_fmaf(weight_of(wd.x, s0 + u), v[u], acc);
     }
-    if (!active) return;
+    if (n >= p.dv) return;
     const float r = acc / wd.y;
     p.out[int64_t(h) * p.ldo + n] = r;
     if (p.outb) p.outb[int64_t(h) * p.ldob + n] = to_bf16_bits(r);
 }
 
+// BATCH: spans loaded at once
+template <int BATCH>
 __device__ __forceinline__ void merge_block_wide(const AttnParams& p, int blk) {
 #pragma clang fp contract(off)
     const int tid = static_cast<int>(threadIdx.x);
     const int n_cb = (p.dv + 4 * kMergeWideThreads - 1) / (4 * kMergeWideThreads);
     const int h = blk / n_cb;
     const int c = (blk - h * n_cb) * 4 * kMergeWideThreads + 4 * tid;
-    const int lane = tid & 63;
-    const int hb = h / p.hbh, hl = h - hb * p.hbh;
-    const int64_t base = int64_t(hb) * p.nsp * p.hbh + hl;
-    const float* src = p.part_o + base * p.dv + c;
-    const int64_t o_step = int64_t(p.hbh) * p.dv;
-    const bool active = c < p.dv;
-    f32x4 v[kMergeWideBatch];
+    MergeHead mh;
+    mh.init(p, h, tid & 63);
+    f32x4 v[BATCH];
 #pragma unroll
-    for (int u = 0; u < kMergeWideBatch; ++u)
-        v[u] = (active && u < p.nsp) ? *reinterpret_cast<const f32x4*>(src + u * o_step) : f32x4{0.f, 0.f, 0.f, 0.f};
-    const float2 wd = merge_weights(p, base, lane);
+    for (int u = 0; u < BATCH; ++u)
+        v[u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(mh.rsrc, mh.at(p, u, c), 0, 0));
+    const float2 wd = merge_weights(mh.m_l);
     f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int s0 = 0; s0 < p.nsp; s0 += kMergeWideBatch) {
+    for (int s0 = 0; s0 < p.nsp; s0 += BATCH) {
         if (s0 > 0) {
 #pragma unroll
-            for (int u = 0; u < kMergeWideBatch; ++u)
-                v[u] = (active && s0 + u < p.nsp) ? *reinterpret_cast<const f32x4*>(src + (s0 + u) * o_step)
-                                                  : f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int u = 0; u < BATCH; ++u)
+                v[u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(mh.rsrc, mh.at(p, s0 + u, c), 0, 0));
         }
 #pragma unroll
-        for (int u = 0; u < kMergeWideBatch; ++u)
-            if (s0 + u < p.nsp) {
-                const float wu = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wd.x), s0 + u));
+        for (int u = 0; u < BATCH; ++u) {
+            const float wu = weight_of(wd.x, s0 + u);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf(wu, v[u][e], acc[e]);
-            }
+            for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf(wu, v[u][e], acc[e]);
+        }
     }
-    if (!active) return;
+    if (c >= p.dv) return;
     f32x4 r;
 #pragma unroll
     for (int e = 0; e < 4; ++e) r[e] = acc[e] / wd.y;

@@ -204,6 +204,18 @@ def test_attention_wide_head_blocks_match_narrow_bit_for_bit():
     assert_parity(out, ref, ref_abs, what="attention 128 heads x 32768 positions, default partition")
 
 
+@pytest.mark.parametrize("heads,seq,splits", [(5, 70001, 0), (33, 9000, 8), (128, 8300, 9), (20, 33000, 17), (1, 4200, 33)])
+def test_attention_long_spans_and_merge_batches(heads, seq, splits):
+    # spans of eight chunks and more, whose workgroups touch later chunks (shared by 4, 12 or 16 of
+    # them, ragged ends), and merges of up to 16, 32 and 64 spans
+    q, kv, scale = syn.attention_case(60 + heads, heads, seq)
+    out = torch.full((heads, 512), float("nan"), dtype=torch.float32, device="cuda")
+    nmm.nmm_latent_attention_ex(dev16(q, syn.BF16), dev16(kv, syn.BF16), out, scale, splits=splits)
+    torch.cuda.synchronize()
+    ref, ref_abs = oracle.latent_attention(q, kv, scale, dqk=576, dv=512)
+    assert_parity(out, ref, ref_abs, what=f"attention {heads} heads x {seq} positions, splits {splits}")
+
+
 def test_attention_wide_head_blocks_general_shape():
     # the general (not 576 / 512) kernel in blocks of 32 heads: 160 heads over 32 spans would take
     # 320 workgroups in blocks of 16; the same heads in two calls of 80 stay in blocks of 16 (160

@@ -483,6 +483,29 @@ def test_attention_spans_and_workspace_serve_both_head_blocks(heads, seq, splits
     assert ws == ticket + -(-heads // 32) * 32 * nsp * (dv + 2) * 4
 
 
+@pytest.mark.parametrize("nb", [1, 2, 3, 4, 5, 8, 16])
+@pytest.mark.parametrize("ld_kv", [576, 584, 16384])
+def test_attention_touches_stay_in_the_chunk(nb, ld_kv):
+    """attention_block's touches of a later chunk: nb workgroups of a span take a share of its 64 x 18
+    64-byte pieces, two per thread.  No piece is taken twice, every one is from three workgroups on, and
+    each lies in the chunk's rows within the staged 576 columns (the buffer's range check covers rows past
+    the cache)."""
+    pieces, rows = 18, 64
+    share = -(-rows * pieces // nb)
+    seen = np.zeros((rows, pieces), int)
+    tid = np.arange(256)
+    for hbv in range(nb):
+        for i in range(2):
+            v = tid + 256 * i
+            u = hbv * share + v
+            row, c = u // pieces, u % pieces
+            ok = (v < share) & (row < rows)
+            np.add.at(seen, (row[ok], c[ok]), 1)
+            off = row[ok] * ld_kv * 2 + c[ok] * 64
+            assert np.all(off + 4 <= ((rows - 1) * ld_kv + 576) * 2)
+    assert seen.max() == 1 and (nb < 3 or seen.min() == 1)
+
+
 @pytest.mark.parametrize("heads,dv,nsp,hbh", [(128, 512, 16, 16), (128, 512, 16, 32), (70, 512, 3, 16),
                                              (20, 64, 5, 32), (5, 272, 64, 16), (33, 16, 2, 32)])
 def test_merge_blocks_cover_every_output_once(heads, dv, nsp, hbh):
