@@ -63,6 +63,7 @@ struct KParams {
     int n_full, full_lg, tail_chunks, tail_lg;
     int ks_full, rows_full, ks_tail, rows_tail, ks_max;
     int items, mblocks, n_panels;
+    int by_xcd;            // 1: items in runs per XCD, slice by slice (item_of)
 };
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
@@ -149,14 +150,15 @@ __device__ __forceinline__ void prefetch(i32x4 (&buf)[U], const Stream& st) {
 // a fresh register would have to be copied back at the end of the iteration, which waits for
 // it), and a scheduling barrier keeps each reload next to its multiply.  The steady-state loop
 // has no branches, so the wait counters track each load.
-template <int DT, int MT, int U, bool GUARD>
-__device__ __forceinline__ void stream_rows(float (&acc)[MT][8], i32x4 (&buf)[U], const Stream& st,
+// Step s adds into accumulator s % NA, which shortens the chain of fp32 additions.
+template <int DT, int MT, int NA, int U, bool GUARD>
+__device__ __forceinline__ void stream_rows(float (&acc)[NA][MT][8], i32x4 (&buf)[U], const Stream& st,
                                             int nsteps, const float* __restrict__ xs, int xs_step) {
     int s = 0;
     for (; s + U < nsteps; s += U) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            fma_chunk<DT, MT>(acc, buf[u], xs + (s + u) * xs_step);
+            fma_chunk<DT, MT>(acc[u % NA], buf[u], xs + (s + u) * xs_step);
             const int sn = s + U + u;
             buf[u] = load_chunk<GUARD>(st.rsrc, st.off + sn * st.step_bytes, st.row + sn * st.rstep < st.K);
             // keep the reload here: sunk to the end of the iteration it would leave nothing in
@@ -165,7 +167,7 @@ __device__ __forceinline__ void stream_rows(float (&acc)[MT][8], i32x4 (&buf)[U]
         }
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u) fma_chunk<DT, MT>(acc, buf[u], xs + (s + u) * xs_step);
+    for (int u = 0; u < U; ++u) fma_chunk<DT, MT>(acc[u % NA], buf[u], xs + (s + u) * xs_step);
 }
 
 // How y and its bf16 copy are stored.  After MatMul 2 the fp32 y is read by the launch's last
@@ -253,13 +255,22 @@ template <int MT>
 __device__ __forceinline__ Item item_of(const KParams& p, uint32_t bid, int tid) {
     Item it;
     const int lane = tid & 63, wave = tid >> 6;
-    const int item = static_cast<int>(bid % uint32_t(p.items));
+    int item = static_cast<int>(bid % uint32_t(p.items));
     const uint32_t bm = bid / uint32_t(p.items);
     it.mb = static_cast<int>(bm % uint32_t(p.mblocks));
     it.b = bm / uint32_t(p.mblocks);
+    if (p.by_xcd) {   // workgroup ids are dealt to the 8 XCDs in turn: give each XCD a run of items
+        const int x = item & 7, q = p.items >> 3, r = p.items & 7;
+        item = x * q + min(x, r) + (item >> 3);
+    }
     if (item < p.n_full * p.ks_full) {
-        it.panel = item / p.ks_full;
-        it.slice = item - it.panel * p.ks_full;
+        if (p.by_xcd) {
+            it.slice = item / p.n_full;
+            it.panel = item - it.slice * p.n_full;
+        } else {
+            it.panel = item / p.ks_full;
+            it.slice = item - it.panel * p.ks_full;
+        }
         it.lg = p.full_lg;
         it.ks = p.ks_full;
         it.rows = p.rows_full;
@@ -362,9 +373,10 @@ __device__ __forceinline__ void reduce_item(const KParams& p, const Item& it, fl
         lds_barrier();
         for (int o = tid; o < MG * pcols; o += kThreads) {
             const int mm = o / pcols, col = o - mm * pcols;
-            float v = lds[mm * pcols + col];
+            double wide = lds[mm * pcols + col];   // waves and slices add in fp64: one rounding per hand-over
 #pragma unroll
-            for (int w = 1; w < kWaves; ++w) v += lds[(w * MG + mm) * pcols + col];
+            for (int w = 1; w < kWaves; ++w) wide += double(lds[(w * MG + mm) * pcols + col]);
+            const float v = float(wide);
             const int m = g + mm;
             const int n = it.chunk0 * 8 + col;
             if (it.ks == 1) {
@@ -379,44 +391,46 @@ __device__ __forceinline__ void reduce_item(const KParams& p, const Item& it, fl
 }
 
 // Gather, part 2 (the panel's last workgroup only): every output of the panel sums its K-slices
-// in slice order; the loads of R outputs x QB slices are all in flight before any is added.
+// in slice order, in fp64; the loads of R outputs x QB slices are all in flight before any is added.  They
+// are range-checked buffer loads at device scope, out of range past the last slice or output: a branch
+// per load keeps them from going out together.
+constexpr int kDevice = 16;   // sc1: device scope, past the XCD's L2 (handoff.h)
+
 template <int MT, int SM>
 __device__ __forceinline__ void gather_panel(const KParams& p, const Item& it, int tid) {
     constexpr int R = (MT * 2 < 8) ? MT * 2 : 8;   // outputs per thread per pass (pcols <= 512)
     constexpr int QB = 32 / R;                      // slices per batch
-    const int pcols = it.cw * 8;
+    const int lg = it.lg + 3, pcols = 1 << lg;
     const int n_out = MT * pcols;
-    const int64_t pbase = part_base<MT>(p, it);
+    constexpr uint32_t kSlice = MT * kPanelCols * 4;   // bytes of a slice's partials
+    const __amdgpu_buffer_rsrc_t pr = make_rsrc(p.part + part_base<MT>(p, it), uint32_t(it.ks) * kSlice);
     for (int o0 = tid; o0 < n_out; o0 += R * kThreads) {
-        float sum[R];
+        uint32_t off[R];
+        double sum[R];
 #pragma unroll
-        for (int r = 0; r < R; ++r) sum[r] = 0.f;
+        for (int r = 0; r < R; ++r) {
+            const int o = o0 + r * kThreads;
+            off[r] = o < n_out ? uint32_t((o >> lg) * kPanelCols + (o & (pcols - 1))) * 4u : kOutOfRange;
+            sum[r] = 0.0;
+        }
         for (int q0 = 0; q0 < it.ks; q0 += QB) {
             float v[R][QB];
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const int o = o0 + r * kThreads;
-                const int m = o / pcols, col = o - m * pcols;
-                const float* src = p.part + pbase + m * kPanelCols + col;
-#pragma unroll
-                for (int u = 0; u < QB; ++u)
-                    v[r][u] = (o < n_out && q0 + u < it.ks)
-                                  ? __hip_atomic_load(src + int64_t(q0 + u) * (MT * kPanelCols), __ATOMIC_RELAXED,
-                                                      __HIP_MEMORY_SCOPE_AGENT)
-                                  : 0.f;
-            }
 #pragma unroll
             for (int r = 0; r < R; ++r)
 #pragma unroll
                 for (int u = 0; u < QB; ++u)
-                    if (q0 + u < it.ks) sum[r] += v[r][u];
+                    v[r][u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                        pr, q0 + u < it.ks ? off[r] + uint32_t(q0 + u) * kSlice : kOutOfRange, 0, kDevice));
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int u = 0; u < QB; ++u) sum[r] += double(v[r][u]);
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int o = o0 + r * kThreads;
-            const int m = o / pcols, col = o - m * pcols;
-            const int n = it.chunk0 * 8 + col;
-            if (o < n_out && it.m0 + m < p.M && n < p.N) store_out<SM>(p, it.b, it.m0 + m, n, sum[r]);
+            const int m = o >> lg, n = it.chunk0 * 8 + (o & (pcols - 1));
+            if (o < n_out && it.m0 + m < p.M && n < p.N) store_out<SM>(p, it.b, it.m0 + m, n, float(sum[r]));
         }
     }
 }
@@ -441,15 +455,23 @@ __device__ __forceinline__ void stream_item(const KParams& p, const Item& it, fl
     __syncthreads();
 
     // ---- compute: stream this workgroup's rows of the panel
+    constexpr int NA = MT <= 2 ? 2 : 1;
+    float part[NA][MT][8];
 #pragma unroll
-    for (int m = 0; m < MT; ++m)
+    for (int a = 0; a < NA; ++a)
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[m][j] = 0.f;
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) part[a][m][j] = 0.f;
     {
         const int nsteps = it.rows / it.rstep;
         const float* xs = lds + it.rin * MT;
-        stream_rows<DT, MT, U, true>(acc, buf, st, nsteps, xs, it.rstep * MT);
+        stream_rows<DT, MT, NA, U, true>(part, buf, st, nsteps, xs, it.rstep * MT);
     }
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[m][j] = NA == 2 ? part[0][m][j] + part[NA - 1][m][j] : part[0][m][j];
     __syncthreads();   // x slice no longer needed: LDS becomes the reduction buffer
 }
 
@@ -993,6 +1015,10 @@ KParams make_params(const GemvArgs& a, const GemvPlan& p, unsigned* tickets, flo
     kp.items = p.items;
     kp.mblocks = p.mblocks;
     kp.n_panels = p.n_full + (p.tail_chunks ? 1 : 0);
+    // rows that start inside a cache line: neighbouring panels share the line between them, so they go to
+    // one XCD, whose L2 then reads it once (a multiple of 8 slices does that in the plain order too; [16384, 2500] 26.7 -> 20.8 us, [8192, 6000] 23.9 -> 19.9,
+    // [6000, 4500] 15.9 -> 13.5).  Rows of whole lines gain nothing (W_O 38.7 and 38.8, down 9.2 and 9.3).
+    kp.by_xcd = a.batch == 1 && p.mblocks == 1 && kp.row_bytes % 128 != 0 && p.ks_full % 8 != 0 ? 1 : 0;
     if (p.split()) {
         kp.tickets = tickets;
         kp.part = part;
