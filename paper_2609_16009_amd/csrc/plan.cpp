@@ -97,6 +97,47 @@ nmm_status validate_gemv(const GemvArgs& a, int path) {
     return NMM_OK;
 }
 
+// Panels and K-slices of a single 1- or 2-row product of up to 100 MB: chunks per panel, slices and
+// row-steps in flight.  Measured on MI355X at one row over panels of 8 to 64 chunks, 4 to 16 steps and
+// grids of 64 to 512 (best of each against the choice before, 128-byte panels and a power-of-two split):
+//  * no K-split where 150 to 256 panels of some width cover the row: nothing is handed over (W_UQ [1536,
+//    24576] 192 panels 14.4 us, [1536, 12288] 10.3; [700, 20000] 157 panels 9.0 against 12.3);
+//  * else panels of 16 chunks (256 bytes: whole lines, also where rows start inside one) and as many
+//    slices, up to 8, as keep one workgroup per CU: [3000, 3000] 8.4 against 10.5, [4099, 5003] 13.1
+//    against 15.2, [4096, 7168] 13.5 against 15.5, [8192, 4096] 14.9 against 16.6, [1536, 6144] 8.1
+//    against 9.1;
+//  * panels of 8 chunks where that would need more slices, whose gather is a serial tail ([7168, 2112] 7
+//    slices 9.3, 16 chunks and 14 slices 10.5; [7168, 576] 7.3 and 7.7);
+//  * no split of K up to 512 either ([512, 512] 4.0, two slices 5.4);
+//  * up to 12 MB about 144 workgroups, as the streams are short ([2048, 2048] 128 workgroups 6.6, 256
+//    6.8; [4096, 1024] 128 7.2), and at most 4 slices of the wider panels ([2048, 2048] with 8 7.1).
+// Eight row-steps in flight serve a split K as well as sixteen; a long unsplit stream keeps sixteen.
+struct NarrowChoice {
+    int cw = 0, ks = 1, unroll = 16;
+};
+NarrowChoice narrow_plan(int64_t K, int64_t chunks, int64_t w_bytes) {
+    NarrowChoice c;
+    for (int cw : {32, 16, 8}) {
+        const int64_t panels = cdiv(chunks, cw);
+        if (panels >= 150 && panels <= 256) {
+            c.cw = cw;
+            c.unroll = K >= 1024 ? 16 : 8;
+            return c;
+        }
+    }
+    if (K <= 512) {
+        c.cw = 8;
+        return c;
+    }
+    const bool small = w_bytes <= int64_t(12) << 20;
+    const int64_t want = small ? 144 : 256;
+    const int64_t wide = want / cdiv(chunks, 16);
+    c.cw = wide <= (small ? 4 : 10) ? 16 : 8;
+    c.ks = static_cast<int>(std::max<int64_t>(1, c.cw == 16 ? std::min<int64_t>(8, wide) : std::min<int64_t>(16, want / cdiv(chunks, 8))));
+    c.unroll = 8;
+    return c;
+}
+
 // The matrix-core partition: 128-column panels, K-slices of whole 64-row stages, x tiles of
 // 16 or 32 rows.  As many slices as keep the grid within one workgroup per CU: a part-filled second
 // round costs more than shorter slices save (measured on MI355X at 4 / 32 rows, floor(256 / panels)
@@ -178,14 +219,13 @@ nmm_status plan_gemv(int64_t batch, int64_t M, int64_t K, int64_t N, int dt, int
     const int64_t chunks = cdiv(N, 8);
     const int64_t mats = std::max<int64_t>(batch, 1) * q.mblocks;
     const int64_t w_bytes = mats * K * chunks * 16;
-    // Measured on MI355X over the decode shapes: 1- and 2-row tiles stream best with about one
-    // workgroup per compute unit -- for weights up to 100 MB with 16 row-steps in flight per lane
-    // and as few K-slices as the panel count allows (the split-K gather is a serial tail), for
-    // larger weights with 8 in flight and panels up to 512 columns.  Taller tiles keep 4 in
-    // flight and more workgroups.
+    // Measured on MI355X: 1- and 2-row tiles stream best with about one workgroup per compute unit.
+    // Weights up to 100 MB ("deep") choose panels and slices by narrow_plan below; larger ones take panels
+    // up to 512 columns with 8 row-steps in flight.  Taller tiles keep 4 in flight and more workgroups.
     const bool narrow_m = q.mt <= 2;
     const bool deep = narrow_m && w_bytes <= int64_t(100) << 20;
-    q.unroll = unroll > 0 ? unroll : static_cast<int>(tuned("NMM_GEMV_UNROLL", deep ? 16 : narrow_m ? 8 : 4));
+    const NarrowChoice nc = deep && mats == 1 && K > 0 && N > 0 ? narrow_plan(K, chunks, w_bytes) : NarrowChoice{};
+    q.unroll = unroll > 0 ? unroll : static_cast<int>(tuned("NMM_GEMV_UNROLL", nc.cw ? nc.unroll : deep ? 16 : narrow_m ? 8 : 4));
     if (q.unroll != 2 && q.unroll != 4 && q.unroll != 8 && q.unroll != 16) q.unroll = 8;
     if (q.unroll == 16 && q.mt > 2) q.unroll = 8;                  // 16 only for 1- and 2-row tiles
     const int U = q.unroll;
@@ -202,8 +242,9 @@ nmm_status plan_gemv(int64_t batch, int64_t M, int64_t K, int64_t N, int dt, int
     const int64_t want = tuned("NMM_GEMV_TARGET",
                                  narrow_m ? 256 : std::max<int64_t>(256, std::min<int64_t>(768, w_bytes / 100000)));
     while (cw > min_cw && (mats * cdiv(chunks, cw) < 24 || chunks < 2 * cw)) cw /= 2;
-    // deep plans trade K-slices for narrower panels while twice the panels still fit the target
-    if (deep && U == 16 && !tuned_set("NMM_GEMV_MAXCW"))
+    // deep plans of a batch trade K-slices for narrower panels while twice the panels still fit the target
+    if (nc.cw && !tuned_set("NMM_GEMV_MAXCW")) cw = nc.cw;
+    else if (deep && U == 16 && !tuned_set("NMM_GEMV_MAXCW"))
         while (cw > min_cw && 2 * mats * cdiv(chunks, cw) <= want) cw /= 2;
     // K-slices per panel: the power of two nearest want / panels, capped (fewer for tall row
     // tiles, whose partial sums are MT times larger)
@@ -234,11 +275,16 @@ nmm_status plan_gemv(int64_t batch, int64_t M, int64_t K, int64_t N, int dt, int
     int64_t ks_want = 1;
     {
         const double ratio = double(want) / double(std::max<int64_t>(panels_all, 1));
-        if (tuned("NMM_GEMV_KS_ANY", 0) > 0) {
+        if (nc.cw && !tuned_set("NMM_GEMV_TARGET")) {
+            ks_want = nc.ks;
+        } else if (tuned("NMM_GEMV_KS_ANY", 0) > 0) {
             ks_want = std::max<int64_t>(1, std::min<int64_t>(ks_cap, int64_t(ratio + 0.5)));
         } else {
             while (ks_want < ks_cap && double(ks_want) * 1.41421356 < ratio) ks_want *= 2;   // nearest power of two
             ks_want = std::min(ks_want, ks_cap);
+            // one or two rows: not more than one workgroup per CU ([10000, 9001], 36 panels: 7 slices 31.4
+            // us, 8 slices 41.8)
+            if (narrow_m && mats == 1 && ks_want * panels_all > want) ks_want = std::max<int64_t>(1, want / panels_all);
         }
     }
 

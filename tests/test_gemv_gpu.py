@@ -233,6 +233,22 @@ def test_hip_error_reaches_the_caller_as_nmm_err_hip():
     assert_parity(y, y_ref, a_ref)
 
 
+@pytest.mark.parametrize("M", [1, 2])
+@pytest.mark.parametrize("K,N", [(512, 700), (513, 700), (700, 20000), (3000, 3000), (16384, 2500), (1100, 9001), (4099, 5003),
+                                 (7168, 1031), (6000, 9001), (130, 33000)])
+def test_narrow_plans_integer_exact(M, K, N):
+    # one- and two-row plans: unsplit and split, panels of 8, 16 and 32 chunks, items in XCD runs (rows that
+    # start inside a line) and in plain order (ldw a multiple of 64), ragged last panels
+    for ldw in ((N + 7) // 8 * 8, (N + 63) // 64 * 64):
+        c = syn.gemv_case(M + K % 71, M, K, N, syn.BF16, integer=True, ldx=(K + 7) // 8 * 8, ldw=ldw)
+        y = torch.full((M, N + 1), float("nan"), dtype=torch.float32, device="cuda")
+        nmm.nmm_gemv(dev16(c.x, c.dt), dev16(c.W, c.dt), y, N=N, path=nmm.NMM_PATH_GEMV)
+        torch.cuda.synchronize()
+        y_ref, a_ref = oracle.gemv(c.x, c.W, c.dt, K=K, N=N)
+        assert_parity(y[:, :N], y_ref, a_ref, integer=True, what=f"narrow {M}x{K}x{N} ld {ldw}")
+        assert torch.isnan(y[:, N:]).all()
+
+
 def test_infinity_propagates_to_its_column_only():
     c = syn.gemv_case(6, 1, 3000, 700, syn.BF16, ldw=704)
     W = c.W.copy()

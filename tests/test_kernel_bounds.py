@@ -483,6 +483,28 @@ def test_attention_spans_and_workspace_serve_both_head_blocks(heads, seq, splits
     assert ws == ticket + -(-heads // 32) * 32 * nsp * (dv + 2) * 4
 
 
+@pytest.mark.parametrize("n_full,ks_full,ks_tail", [(7, 5, 0), (39, 6, 3), (156, 1, 1), (8, 16, 16), (1, 1, 0), (3, 7, 2)])
+def test_gemv_items_in_xcd_runs_cover_each_once(n_full, ks_full, ks_tail):
+    """item_of's order for rows that start inside a cache line: workgroup ids go to the 8 XCDs in turn,
+    each XCD takes a run of items, and a run walks the panels of one slice after the other.  Every (panel,
+    slice) once, and neighbouring panels of a slice on one XCD except at the seven run boundaries."""
+    items = n_full * ks_full + ks_tail
+    seen, xcd = set(), {}
+    for bid in range(items):
+        x, q, r = bid & 7, items >> 3, items & 7
+        item = x * q + min(x, r) + (bid >> 3)
+        if item < n_full * ks_full:
+            key = (item % n_full, item // n_full)
+        else:
+            key = (n_full, item - n_full * ks_full)
+        assert key not in seen and 0 <= item < items
+        seen.add(key)
+        xcd[key] = bid & 7
+    assert seen == {(p, s) for p in range(n_full) for s in range(ks_full)} | {(n_full, s) for s in range(ks_tail)}
+    split = sum(xcd[(p, s)] != xcd[(p + 1, s)] for p in range(n_full - 1) for s in range(ks_full))
+    assert split <= 7
+
+
 @pytest.mark.parametrize("nb", [1, 2, 3, 4, 5, 8, 16])
 @pytest.mark.parametrize("ld_kv", [576, 584, 16384])
 def test_attention_touches_stay_in_the_chunk(nb, ld_kv):
