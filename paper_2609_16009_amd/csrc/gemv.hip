@@ -799,12 +799,26 @@ __device__ __forceinline__ void kv_entry(const float* src, const KvParams& e, fl
     float* gam = lds + n_all;           // [kv]
     float* red = gam + e.kv;            // [kWaves]
     float ss = 0.f;
-    for (int i = tid; i < n_all; i += kThreads) {
-        const float v = __hip_atomic_load(src + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        vals[i] = v;
-        if (i < e.kv) {
-            gam[i] = __uint_as_float(uint32_t(e.gamma[i]) << 16);
-            ss += v * v;
+    // kPer values per thread and pass, their loads out together (a loop of single loads pays a device-scope
+    // round trip for each: three for 576 values, 1.3 us of MatMul 2's launch)
+    constexpr int kPer = 4;
+    const __amdgpu_buffer_rsrc_t sr = make_rsrc(src, uint32_t(n_all) * 4u), gr = make_rsrc(e.gamma, uint32_t(e.kv) * 2u);
+    for (int i0 = tid; i0 < n_all; i0 += kPer * kThreads) {
+        float v[kPer], g[kPer];
+#pragma unroll
+        for (int u = 0; u < kPer; ++u)   // past the end: zeros
+            v[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(sr, uint32_t(i0 + u * kThreads) * 4u, 0, kDevice));
+#pragma unroll
+        for (int u = 0; u < kPer; ++u)
+            g[u] = __uint_as_float(uint32_t(__builtin_amdgcn_raw_buffer_load_b16(gr, uint32_t(i0 + u * kThreads) * 2u, 0, 0)) << 16);
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int i = i0 + u * kThreads;
+            if (i < n_all) vals[i] = v[u];
+            if (i < e.kv) {
+                gam[i] = g[u];
+                ss += v[u] * v[u];
+            }
         }
     }
     // mean of squares: a fixed butterfly inside each wave, then the waves in order
@@ -859,34 +873,35 @@ __global__ __launch_bounds__(kThreads) void gemv_kv_kernel(const KParams p, cons
     if (s_last) kv_entry(p.y + e.c_off, e, lds, sn, cs);
 }
 
-// A batched GEMV launch (the per-head q_nope . W_UK of the absorbed query) with one extra
-// workgroup, the last, that rotates each head's rope part of the query, q[h, nope : nope+rope]
-// (fp32, from an earlier launch), and writes it as bf16 at q_out[h, kv : kv + rope].
+// A batched GEMV launch (the per-head q_nope . W_UK of the absorbed query) with extra workgroups
+// after its own that rotate each head's rope part of the query, q[h, nope : nope+rope] (fp32, from an
+// earlier launch), and write it as bf16 at q_out[h, kv : kv + rope]: one (head, pair) per thread, so that
+// no thread waits for one head's loads after another's (one workgroup for all heads took 4 round trips at
+// 32 heads and 16 at 128).
 struct QropeParams {
     const float* q;          // [heads, nope + rope] fp32
     uint16_t* q_out;         // [heads, ldq] bf16
     int64_t ldq;
     int heads, nope, kv;
+    uint32_t gemv_grid;      // workgroups of the GEMV
 };
 
 template <int U>
 __global__ __launch_bounds__(kThreads) void gemv_qrope_kernel(const KParams p, const KvParams e, const QropeParams r) {
     extern __shared__ float lds[];
     __shared__ int s_last;
-    if (blockIdx.x == gridDim.x - 1) {
+    if (blockIdx.x >= r.gemv_grid) {
         const int pairs = e.rope / 2;
-        if (pairs == 0) return;
-        const int j = threadIdx.x % pairs, h0 = threadIdx.x / pairs, hstep = kThreads / pairs;
-        if (h0 >= hstep) return;                     // threads past the last whole group of pairs
+        const uint32_t t = (blockIdx.x - r.gemv_grid) * uint32_t(kThreads) + threadIdx.x;
+        const int h = static_cast<int>(t / uint32_t(pairs)), j = static_cast<int>(t - uint32_t(h) * uint32_t(pairs));
+        if (h >= r.heads) return;
+        const float* src = r.q + int64_t(h) * (r.nope + e.rope) + r.nope + 2 * j;
+        const float k0 = src[0], k1 = src[1];
         float sn, cs;
         rope_angle(e, j, &sn, &cs);
-        const int qk = r.nope + e.rope;
-        for (int h = h0; h < r.heads; h += hstep) {
-            const float k0 = r.q[int64_t(h) * qk + r.nope + 2 * j], k1 = r.q[int64_t(h) * qk + r.nope + 2 * j + 1];
-            uint16_t* dst = r.q_out + int64_t(h) * r.ldq + r.kv + 2 * j;
-            dst[0] = to_bf16_bits(k0 * cs - k1 * sn);
-            dst[1] = to_bf16_bits(k0 * sn + k1 * cs);
-        }
+        uint16_t* dst = r.q_out + int64_t(h) * r.ldq + r.kv + 2 * j;
+        dst[0] = to_bf16_bits(k0 * cs - k1 * sn);
+        dst[1] = to_bf16_bits(k0 * sn + k1 * cs);
         return;
     }
     gemv_item<NMM_BF16, 1, U, kStorePlain>(p, blockIdx.x, lds, &s_last);
@@ -1235,8 +1250,10 @@ nmm_status launch_gemv_qrope(const GemvArgs& a, const GemvPlan& p, unsigned* tic
     r.heads = heads;
     r.nope = nope;
     r.kv = kv;
+    r.gemv_grid = static_cast<uint32_t>(p.grid);
     const size_t lds = gemv_lds_bytes(p);
-    const dim3 grid(static_cast<uint32_t>(p.grid + 1)), block(kThreads);
+    const int64_t extra = (int64_t(heads) * (rope / 2) + kThreads - 1) / kThreads;
+    const dim3 grid(static_cast<uint32_t>(p.grid + extra)), block(kThreads);
     switch (p.unroll) {
         case 16: hipLaunchKernelGGL(gemv_qrope_kernel<16>, grid, block, lds, s, kp, kv_p, r); break;
         case 8: hipLaunchKernelGGL(gemv_qrope_kernel<8>, grid, block, lds, s, kp, kv_p, r); break;

@@ -140,7 +140,7 @@ nmm_status launch_gemv_kv(const GemvArgs& a, const GemvPlan& p, unsigned* ticket
 // of `e` from src[0 .. kv + rope), a product an earlier launch on the stream completed.
 nmm_status launch_gemv_entry(const GemvArgs& a, const GemvPlan& p, unsigned* tickets, float* part,
                              const KvEpilogue& e, const float* src, void* stream);
-// A validated M = 1 bf16 batched GEMV plan with one extra workgroup that writes
+// A validated M = 1 bf16 batched GEMV plan with extra workgroups that write
 // bf16(RoPE(q[h, nope : nope + rope], position)) to q_out[h * ldq + kv ..] for every head.
 nmm_status launch_gemv_qrope(const GemvArgs& a, const GemvPlan& p, unsigned* tickets, float* part, const float* q,
                              void* q_out, int64_t ldq, int heads, int nope, int kv, int rope, int64_t position,

@@ -420,6 +420,21 @@ def test_qrope_workgroup_covers_each_pair_once(heads, nope, rope, kv, ldq):
     assert np.all(seen == 1)
 
 
+@pytest.mark.parametrize("heads,rope", [(128, 64), (6, 24), (4, 8), (3, 512), (1, 2), (7, 0), (33, 64)])
+def test_qrope_threads_cover_each_pair_once(heads, rope):
+    """The extra workgroups of the query launch, one (head, pair) per thread: ceil(heads rope / 2 / 256)
+    of them (none without a rope part) write every pair of every head exactly once."""
+    pairs = rope // 2
+    t = np.arange(-(-heads * pairs // THREADS) * THREADS)
+    if pairs == 0:
+        assert t.size == 0
+        return
+    h, j = t // pairs, t % pairs
+    seen = np.zeros((heads, pairs), int)
+    np.add.at(seen, (h[h < heads], j[h < heads]), 1)
+    assert np.all(seen == 1)
+
+
 def default_spans(heads, seq):
     """The default partition before the span is rounded to whole chunks: about 64 (32-head block,
     span) pairs, or spans of at most 8 chunks, or of about 4 (chunks // 4 spans) while a grid of 16-head blocks
