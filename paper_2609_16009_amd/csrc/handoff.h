@@ -3,9 +3,10 @@
 // accumulate, Section III-B) and the count of finished panels before the cache entry.
 //
 // Ordering argument (gfx950 ISA), in place of a release/acquire pair:
-//  * every value handed over is written with device-scope atomic stores (the SC1 scope bits),
-//    which write through the XCD's L2 to the device's coherence point, and read with
-//    device-scope atomic loads, which are served from that point, never from a stale L2 line;
+//  * every value handed over is written with device-scope stores (atomic, or buffer stores with the
+//    SC1 scope bit, the same instructions' modifier), which write through the XCD's L2 to the
+//    device's coherence point, and read with device-scope loads (atomic or buffer loads, SC1), which
+//    are served from that point, never from a stale L2 line;
 //  * a workgroup counts its part in only after `s_waitcnt 0` in every wave and a barrier:
 //    a store's counter is decremented when the coherence point acknowledges it, so all of the
 //    part's stores are visible there before the count is issued;
