@@ -224,9 +224,9 @@ nmm_status prepare(int64_t heads, int64_t seq, int64_t d_qk, int64_t d_v, const 
     p.hbh = a.hbh;
     p.xcd_map = a.xcd_map;
     // Spans of many chunks: the workgroups of a span bring the chunk two ahead into L2, which the double
-    // buffer alone (one chunk per span in flight, 4.7 MB over 64 spans) cannot cover from HBM: 8 heads x
-    // 131072 positions 70.1 -> 56.7 us, 128 x 65536 cold 46.2 -> 41.3, 128 x 32768 cold 29.7 -> 27.4; level
-    // with the cache in the MALL.  Short spans gain nothing (four chunks: 13.0 either way), and beside a
+    // buffer alone (one chunk per span in flight, 4.7 MB over 64 spans) cannot cover from HBM: with the
+    // straight-line merge, 16 heads x 131072 positions 72.9 -> 56.7 us, 128 x 32768 28.4 -> 26.4, 128 x 65536
+    // 39.5 -> 38.3.  Short spans gain nothing (four chunks: 13.0 either way), and beside a
     // GEMV's stream the attention keeps its loads as they are.
     p.touch = hbh == kAloneHeads && a.span >= kTouchMinChunks * kCh ? kTouchAhead : 0;
     p.scale_log2 = scale * 1.4426950408889634f;

@@ -16,9 +16,10 @@
 //  * Sums: a chain of two MFMAs in fp32, then added in fp64 (the vector units are idle), waves
 //    added in fp64 in wave order, one rounding to fp32 at the end.  One fp32 chain over K loses
 //    precision with its length (relative 2-norm error 2.3e-7 at K = 1536, 8.0e-7 at 16384, against
-//    7.1e-8 and 1.3e-7 for fp32 FMAs over 64 lanes); this form measures 4.9e-8 at any K.
-//  * Bound by the weight's bytes up to about 16 rows (W_O 40 us at 2 to 8 rows, 5.9 TB/s), then also
-//    by x from L2, which every workgroup reads whole: 41 us at 16 rows, 52 at 32.
+//    7.1e-8 and 1.3e-7 for fp32 FMAs over 64 lanes); this form measures 4.9e-8 in bf16 and 6.3e-8
+//    in fp16, at any K.
+//  * Bound by the weight's bytes up to about 16 rows (W_O 41 to 43 us, 5.6 TB/s), then also by x from
+//    L2, which every workgroup reads whole: 48 us at 32.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
