@@ -164,7 +164,10 @@ nmm_status plan_mfma(int64_t M, int64_t K, int64_t N, GemvPlan* p) {
     // fewer than 70 % of the CUs in use on a long K: two workgroups per CU, which still fit side by side
     // ([4096, 16640], 130 panels: 28.3 us with 3 slices against 33.8 with one; on K = 1024 11.3 against 10.1)
     if (ks_want * panels * 10 < want * 7 && K >= kMfmaLongK) ks_want = std::max(ks_want, 2 * want / panels);
-    ks_want = std::min(ks_want, ks_cap);
+    // nor more slices than nmm_gemv_noalloc's scratch holds (170 panels of 32 rows: two, not three)
+    const int64_t slice_bytes = panels * q.mt * kMfmaPanelCols * 4;
+    const int64_t fits = (int64_t(NMM_NOALLOC_SCRATCH_BYTES) - kTicketBytes) / slice_bytes;
+    ks_want = std::max<int64_t>(1, std::min(std::min(ks_want, ks_cap), fits));
     int64_t r = rup(cdiv(K, ks_want), kMfmaStageRows);
     int64_t k = cdiv(K, r);
     if (panels > kMaxTickets) {

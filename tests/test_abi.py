@@ -110,6 +110,17 @@ def test_chain_rejects_null_and_bad_dims():
     del bufs
 
 
+@pytest.mark.parametrize("M", [3, 16, 17, 24, 32, 33, 64, 65])
+def test_matrix_core_plans_fit_the_library_scratch(M):
+    """The allocation-free call refuses what its scratch cannot hold, so no matrix-core plan may ask for
+    more: every panel count up to 256, 170 among them, whose three slices of 32 rows would be 64 KB too many."""
+    blocks = (M + (15 if M <= 16 else 31)) // (16 if M <= 16 else 32)
+    for panels in range(1, 257):
+        for K in (64, 2047, 2048, 3072, 7168, 65536):
+            for N in {128 * panels // blocks, max(1, 128 * panels // blocks - 127)}:
+                assert L.nmm_gemv_workspace_size(M, K, N, nmm.NMM_BF16, nmm.NMM_PATH_AUTO) <= nmm.NMM_NOALLOC_SCRATCH_BYTES, (K, N)
+
+
 def test_workspace_init_validates():
     assert L.nmm_workspace_init(None, 16, None) == nmm.NMM_ERR_NULL
     assert L.nmm_workspace_init(ALIGNED + 4, 16, None) == nmm.NMM_ERR_WORKSPACE
