@@ -35,8 +35,9 @@ def sources() -> list[str]:
 
 
 # Sources whose matrix-core accumulators must stay in ordinary VGPRs (the attention's softmax and
-# output stages touch them with vector instructions; in AGPRs each touch costs copies).
-VGPR_FORM = {"attention.hip", "gemv.hip"}
+# output stages touch them with vector instructions, the matrix-core GEMV's fp64 sums read them every
+# stage; in AGPRs each touch costs copies: [14508, 5824] at 40 rows 65.9 us against 63.2).
+VGPR_FORM = {"attention.hip", "gemv.hip", "mfma_gemv.hip"}
 
 
 def _compile(src: str) -> str:

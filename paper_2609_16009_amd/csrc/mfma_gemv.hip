@@ -53,6 +53,10 @@ constexpr int kDevice = 16;                    // sc1: device scope (past the XC
 constexpr uint32_t kOutOfRange = 0x80000000u;
 constexpr int kWStride = kMfmaPanelCols + 8;   // LDS row stride of a W stage (elements)
 constexpr int kXStride = kMfmaStageRows + 8;   // LDS row stride of an x stage (elements)
+// A gather of up to kFewSlices slices has a kernel of its own: batches of 16 (8 at 32 rows) add zeros for the
+// slices that are not there, in fp64, and take 130 registers for the loads ([3072, 22912], 2 slices, at 4 / 16
+// rows 29.1 / 31.2 us with them, 27.4 / 29.8 without; [1536, 12288] at 16 rows 11.5 and 10.8).
+constexpr int kMaxSlices = 16, kFewSlices = 4;
 constexpr int kMfmaDepth = 2;                  // stages in flight per thread (2-4 measured alike)
 
 struct MParams {
@@ -99,12 +103,16 @@ __device__ __forceinline__ i32x4 load_w(const uint16_t* wst, int row0, int col0,
     return i32x4{int(lo.x), int(lo.y), int(hi.x), int(hi.y)};
 }
 
-template <int DT, int MT, int D, bool BF>
+// SLICES: the gather's batch is at most this many K-slices (0: one slice, nothing handed over).  TALL (one
+// slice): x is the A operand, and a lane ends with 4 consecutive rows of one column instead.
+template <int DT, int MT, int D, bool BF, int SLICES, bool TALL>
 __global__ __launch_bounds__(kThreads) void mfma_gemv_kernel(const MParams p) {
     // two stage buffers, each a W tile [64][kWStride] followed by an x tile [MT][kXStride]
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
     __shared__ int s_last;
     constexpr int MTILES = MT / 16;
+    constexpr bool SPLIT = SLICES > 0;
+    static_assert(!(SPLIT && TALL), "partial sums are stored in rows");
     constexpr int kStage = kMfmaStageRows * kWStride + MT * kXStride;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -113,7 +121,7 @@ __global__ __launch_bounds__(kThreads) void mfma_gemv_kernel(const MParams p) {
     const uint32_t bid = blockIdx.x;
     const int item = static_cast<int>(bid % uint32_t(p.items));
     const int mb = static_cast<int>(bid / uint32_t(p.items));
-    const int panel = item / p.ks, slice = item - panel * p.ks;
+    const int panel = SPLIT ? item / p.ks : item, slice = SPLIT ? item - panel * p.ks : 0;
     const int m0 = mb * MT, k0 = slice * p.rows, n0 = panel * kMfmaPanelCols;
     const int stages = (min(p.rows, p.K - k0) + kMfmaStageRows - 1) / kMfmaStageRows;
     const int mrows = min(MT, p.M - m0);
@@ -195,7 +203,7 @@ __global__ __launch_bounds__(kThreads) void mfma_gemv_kernel(const MParams p) {
                 const i32x4 w = load_w<DT>(wst, 32 * kk, 16 * (2 * wave + t), g, j);
 #pragma unroll
                 for (int mt = 0; mt < MTILES; ++mt)
-                    part[mt][t] = mfma<DT>(w, x[mt], kk == 0 && first ? f32x4{0.f, 0.f, 0.f, 0.f} : part[mt][t]);
+                    part[mt][t] = mfma<DT>(TALL ? x[mt] : w, TALL ? w : x[mt], kk == 0 && first ? f32x4{0.f, 0.f, 0.f, 0.f} : part[mt][t]);
             }
         }
         if (last) {
@@ -229,7 +237,23 @@ __global__ __launch_bounds__(kThreads) void mfma_gemv_kernel(const MParams p) {
     auto value = [&](int mt, int t) {
         return f32x4{float(acc[mt][t][0]), float(acc[mt][t][1]), float(acc[mt][t][2]), float(acc[mt][t][3])};
     };
-    if (p.ks == 1) {
+    if constexpr (!SPLIT) {
+        if constexpr (TALL) {
+#pragma unroll
+            for (int mt = 0; mt < MTILES; ++mt)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const f32x4 v = value(mt, t);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int ml = 16 * mt + 4 * g + i, n = n0 + 16 * (2 * wave + t) + j;
+                        if (ml >= mrows || n >= p.N) continue;
+                        if (!BF || p.y) p.y[int64_t(m0 + ml) * p.ldy + n] = v[i];
+                        if constexpr (BF) p.ybf[int64_t(m0 + ml) * p.ldyb + n] = to_bf16_mode(v[i], p.away);
+                    }
+                }
+            return;
+        }
 #pragma unroll
         for (int mt = 0; mt < MTILES; ++mt)
 #pragma unroll
@@ -261,7 +285,7 @@ __global__ __launch_bounds__(kThreads) void mfma_gemv_kernel(const MParams p) {
     // every piece of the panel sums its slices in slice order in fp64; the loads of PER pieces x QB
     // slices are all in flight before any is added (rows past M load nothing)
     constexpr int PER = kSlicePieces / kThreads;            // pieces per thread (2 or 4)
-    constexpr int QB = 32 / PER;                            // slices per batch
+    constexpr int QB = SLICES < 32 / PER ? SLICES : 32 / PER;   // slices per batch
     const int n_out = mrows * kQuads;
     double sum[PER][4];
 #pragma unroll
@@ -294,12 +318,26 @@ __global__ __launch_bounds__(kThreads) void mfma_gemv_kernel(const MParams p) {
     }
 }
 
+template <int DT, int MT, bool BF>
+void launch_bf(const MParams& mp, int64_t grid, size_t lds, hipStream_t s) {
+    const dim3 g(static_cast<uint32_t>(grid)), block(kThreads);
+    if (mp.ks > kFewSlices) {
+        hipLaunchKernelGGL((mfma_gemv_kernel<DT, MT, kMfmaDepth, BF, kMaxSlices, false>), g, block, lds, s, mp);
+    } else if (mp.ks > 1) {
+        hipLaunchKernelGGL((mfma_gemv_kernel<DT, MT, kMfmaDepth, BF, kFewSlices, false>), g, block, lds, s, mp);
+    } else if ((!mp.y || wide_f32(mp.y, mp.ldy, 0)) && (!BF || wide_bf16(mp.ybf, mp.ldyb, 0))) {
+        hipLaunchKernelGGL((mfma_gemv_kernel<DT, MT, kMfmaDepth, BF, 0, false>), g, block, lds, s, mp);
+    } else {
+        // rows that take no wide store: 16 lanes store 64 bytes of a row, where four columns a lane would be four
+        // stores of every fourth column ([1022, 33335] at 13 / 32 rows 23.9 / 25.8 us against 25.0 / 28.0)
+        hipLaunchKernelGGL((mfma_gemv_kernel<DT, MT, kMfmaDepth, BF, 0, true>), g, block, lds, s, mp);
+    }
+}
+
 template <int DT, int MT>
 void launch_mt(const MParams& mp, int64_t grid, size_t lds, hipStream_t s) {
-    if (mp.ybf)
-        hipLaunchKernelGGL((mfma_gemv_kernel<DT, MT, kMfmaDepth, true>), dim3(static_cast<uint32_t>(grid)), dim3(kThreads), lds, s, mp);
-    else
-        hipLaunchKernelGGL((mfma_gemv_kernel<DT, MT, kMfmaDepth, false>), dim3(static_cast<uint32_t>(grid)), dim3(kThreads), lds, s, mp);
+    if (mp.ybf) launch_bf<DT, MT, true>(mp, grid, lds, s);
+    else launch_bf<DT, MT, false>(mp, grid, lds, s);
 }
 
 }  // namespace

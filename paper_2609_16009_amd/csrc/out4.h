@@ -1,4 +1,4 @@
-// Four consecutive columns of one output row (device code only).
+// Four consecutive columns of one output row.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -11,10 +11,10 @@ namespace nmm {
 
 // Whether the fp32 rows and the bf16 rows of an output take one wide store per four columns: only
 // where every row starts on that boundary (the ABI asks for 4- and 2-byte alignment only).
-__device__ __forceinline__ bool wide_f32(const float* y, int64_t ldy, int64_t sy) {
+__host__ __device__ __forceinline__ bool wide_f32(const float* y, int64_t ldy, int64_t sy) {
     return ((reinterpret_cast<uintptr_t>(y) | uintptr_t(ldy * 4) | uintptr_t(sy * 4)) & 15u) == 0;
 }
-__device__ __forceinline__ bool wide_bf16(const uint16_t* y, int64_t ldy, int64_t sy) {
+__host__ __device__ __forceinline__ bool wide_bf16(const uint16_t* y, int64_t ldy, int64_t sy) {
     return ((reinterpret_cast<uintptr_t>(y) | uintptr_t(ldy * 2) | uintptr_t(sy * 2)) & 7u) == 0;
 }
 

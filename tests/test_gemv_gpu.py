@@ -416,6 +416,32 @@ def test_mfma_slices_integer_exact(M, K, N):
             assert torch.isnan(y[:, N:]).all(), "columns past N were written"
 
 
+@pytest.mark.parametrize("M", [3, 16, 17, 33])
+@pytest.mark.parametrize("K,N", [(130, 33335), (70, 33336), (1024, 9001), (520, 520)])
+def test_mfma_output_forms_integer_exact(M, K, N):
+    # one slice (261 panels), three and eight; fp32 rows and bf16 rows on and off the boundary of their wide
+    # stores, together and alone; the columns past N keep what they held
+    c = syn.gemv_case(M + K, M, K, N, syn.BF16, integer=True, ldx=(K + 7) // 8 * 8, ldw=(N + 7) // 8 * 8)
+    y_ref, a_ref = oracle.gemv(c.x, c.W, c.dt, K=K, N=N)
+    b_ref = oracle.round_bf16(y_ref.astype(np.float32))
+    x, W = dev16(c.x, c.dt), dev16(c.W, c.dt)
+    on, off = (N + 3) // 4 * 4 + 4, (N + 3) // 4 * 4 + 5
+    for ldy, ldyb in ((on, on), (off, on), (on, off), (off, off), (None, on), (None, off), (off, None)):
+        y = torch.full((M, ldy), float("nan"), dtype=torch.float32, device="cuda") if ldy else None
+        yb = torch.full((M, ldyb), float("nan"), dtype=torch.bfloat16, device="cuda") if ldyb else None
+        if yb is None:
+            nmm.nmm_gemv(x, W, y, N=N)
+        else:
+            nmm.nmm_gemv_bf16(x, W, yb, N=N, y=y)
+        torch.cuda.synchronize()
+        if y is not None:
+            assert_parity(y[:, :N], y_ref, a_ref, integer=True, what=f"fp32 rows {M}x{K}x{N}, ldy {ldy}, ldyb {ldyb}")
+            assert torch.isnan(y[:, N:]).all(), "columns past N were written"
+        if yb is not None:
+            assert np.array_equal(host_bits(yb)[:, :N], b_ref), f"bf16 rows {M}x{K}x{N}, ldy {ldy}, ldyb {ldyb}"
+            assert torch.isnan(yb[:, N:]).all(), "columns past N were written"
+
+
 @pytest.mark.parametrize("M", [1, 2, 3, 4, 5, 8, 16, 17, 32])
 def test_uq_sweep_mfma_path(M):
     check_case(syn.uq_sweep(min(M, 32)) if M <= 32 else None, path=nmm.NMM_PATH_MFMA)
