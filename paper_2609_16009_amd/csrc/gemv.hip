@@ -264,13 +264,11 @@ __device__ __forceinline__ Item item_of(const KParams& p, uint32_t bid, int tid)
         item = x * q + min(x, r) + (item >> 3);
     }
     if (item < p.n_full * p.ks_full) {
-        if (p.by_xcd) {
-            it.slice = item / p.n_full;
-            it.panel = item - it.slice * p.n_full;
-        } else {
-            it.panel = item / p.ks_full;
-            it.slice = item - it.panel * p.ks_full;
-        }
+        // one division for both orders: of one in each branch, the compiler does both (0.13 us of a 4.1 us call)
+        const int d = p.by_xcd ? p.n_full : p.ks_full;
+        const int quot = item / d, rem = item - quot * d;
+        it.panel = p.by_xcd ? rem : quot;
+        it.slice = p.by_xcd ? quot : rem;
         it.lg = p.full_lg;
         it.ks = p.ks_full;
         it.rows = p.rows_full;
