@@ -60,7 +60,6 @@ constexpr int kDefaultFitChunks = 4;      // or this many while one workgroup pe
 constexpr int kDefaultMinChunks = 2;      // but spans of at least this many chunks (one-chunk spans merge
                                           // more partials than their parallelism saves)
 constexpr int kTouchMinChunks = 8;        // spans of this many chunks touch the chunk kTouchAhead ahead
-constexpr int kTouchAhead = 2;
 constexpr int kComputeUnits = 256;        // MI355X; an attention workgroup holds a CU (its LDS)
 
 // Attention launch workgroups of HT head tiles, each taking 4 NTW of d_v's 16-column tiles (of
@@ -228,7 +227,7 @@ nmm_status prepare(int64_t heads, int64_t seq, int64_t d_qk, int64_t d_v, const 
     // straight-line merge, 16 heads x 131072 positions 72.9 -> 56.7 us, 128 x 32768 28.4 -> 26.4, 128 x 65536
     // 39.5 -> 38.3.  Short spans gain nothing (four chunks: 13.0 either way), and beside a
     // GEMV's stream the attention keeps its loads as they are.
-    p.touch = hbh == kAloneHeads && a.span >= kTouchMinChunks * kCh ? kTouchAhead : 0;
+    out->touch = hbh == kAloneHeads && a.span >= kTouchMinChunks * kCh;
     p.scale_log2 = scale * 1.4426950408889634f;
     p.kv_extent = static_cast<uint32_t>(extent);
     p.q_extent = static_cast<uint32_t>(q_extent);
@@ -257,18 +256,21 @@ nmm_status launch_attention_merge(const AttnLaunch& l, hipStream_t s) {
     if (l.merge_grid == 0) return NMM_OK;
     static_assert(4 * kMergeWideThreads == kMergeThreads, "the two merge forms cut a head's columns alike");
     const dim3 grid(static_cast<uint32_t>(l.merge_grid)), block(kMergeWideThreads);
-    // every span's loads in one batch: with batches of 16, 64 heads x 64 spans took 20.5 us with the
-    // attention where 64 at once takes 17.3, 16 heads x 33 spans 11.8 and 10.1
+    // every span's loads in one batch, and not many more than there are spans: with batches of 16, 64 heads x 64
+    // spans took 20.5 us with the attention where 64 at once takes 17.3, 16 heads x 33 spans 11.8 and 10.1; 8
+    // heads x 200 positions (2 spans) 8.1 and 7.7, 128 x 600 (5 spans) 9.7 and 9.3
     if (l.p.nsp > 32) hipLaunchKernelGGL(attention_merge_kernel<64>, grid, block, 0, s, l.p);
     else if (l.p.nsp > 16) hipLaunchKernelGGL(attention_merge_kernel<32>, grid, block, 0, s, l.p);
-    else hipLaunchKernelGGL(attention_merge_kernel<16>, grid, block, 0, s, l.p);
+    else if (l.p.nsp > 8) hipLaunchKernelGGL(attention_merge_kernel<16>, grid, block, 0, s, l.p);
+    else if (l.p.nsp > 4) hipLaunchKernelGGL(attention_merge_kernel<8>, grid, block, 0, s, l.p);
+    else hipLaunchKernelGGL(attention_merge_kernel<4>, grid, block, 0, s, l.p);
     return hipGetLastError() == hipSuccess ? NMM_OK : NMM_ERR_HIP;
 }
 
 nmm_status launch_attention_kernel(const AttnLaunch& l, hipStream_t s) {
     if (l.grid == 0) return NMM_OK;
     if (l.variant != kAttnExact) return launch_attention<false, false>(l.p, l.grid, l.vsplit, s);
-    return l.p.touch > 0 ? launch_attention<true, true>(l.p, l.grid, l.vsplit, s)
+    return l.touch ? launch_attention<true, true>(l.p, l.grid, l.vsplit, s)
                          : launch_attention<true, false>(l.p, l.grid, l.vsplit, s);
 }
 

@@ -41,6 +41,10 @@ constexpr uint32_t kOutOfRange = 0x80000000u;
 // more than this (log2 units), so probabilities stay below 2^kLazyTh and the rescale is rare.
 constexpr float kLazyTh = 8.f;
 
+// A long span's touches run this many chunks ahead (a constant and no argument: one more word of arguments took
+// every attention launch 0.07 us more).
+constexpr int kTouchAhead = 2;
+
 struct AttnParams {
     const uint16_t* q;
     int64_t ldq;
@@ -58,7 +62,6 @@ struct AttnParams {
     int nsp, span, n_hb;
     int hbh;            // heads per block (16 per head tile)
     int xcd_map;        // 1: the head blocks of a span grouped on one XCD (grid padded to 8 spans)
-    int touch;          // chunks ahead whose cache lines a span's workgroups bring into L2 (0: none)
     float scale_log2;   // scale * log2(e): scores are kept in log2 units
     uint32_t kv_extent; // bytes of the cache that may be read
     uint32_t q_extent;  // bytes of q that may be read
@@ -348,13 +351,13 @@ __device__ __forceinline__ void attention_block(const AttnParams p, int bid) {
 
         // bring a later chunk's lines into L2 (the values go to a sink nothing reads); these loads come
         // after the staging's, so the wait at the chunk's end can leave them in flight
-        const bool touched = TOUCH && ck + p.touch < nchunks;
+        const bool touched = TOUCH && ck + kTouchAhead < nchunks;
         if (TOUCH && touched) {
             uint32_t* const sink = touch_sink() + 64 * wave;
 #pragma unroll
             for (int i = 0; i < kTouch; ++i)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                    kvr, (lds_void*)sink, 4, toff[i] == kOutOfRange ? kOutOfRange : toff[i] + uint32_t(c0 + p.touch * kCh) * row_bytes, 0, 0, 0);
+                    kvr, (lds_void*)sink, 4, toff[i] == kOutOfRange ? kOutOfRange : toff[i] + uint32_t(c0 + kTouchAhead * kCh) * row_bytes, 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         }
 
@@ -613,9 +616,9 @@ struct MergeHead {
         m_l = float2{-INFINITY, 0.f};
         if (lane < p.nsp) m_l = *reinterpret_cast<const float2*>(p.part_ml + (base + int64_t(lane) * p.hbh) * 2);
     }
-    __device__ __forceinline__ uint32_t at(const AttnParams& p, int span, int c) const {
-        return span < p.nsp && c < p.dv ? uint32_t(span) * o_step + uint32_t(c) * 4u : kOutOfRange;
-    }
+    // Column c's offset in the first span; span s lies s o_step on, and one past the last is out of range by itself
+    // (o_step covers a row), so no load needs a check of its own.
+    __device__ __forceinline__ uint32_t at(const AttnParams& p, int c) const { return c < p.dv ? uint32_t(c) * 4u : kOutOfRange; }
 };
 __device__ __forceinline__ float weight_of(float w, int span) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), span));
@@ -631,18 +634,19 @@ __device__ __forceinline__ void merge_block(const AttnParams& p, int blk, int ti
     const int n = cb * kMergeThreads + tid;
     MergeHead mh;
     mh.init(p, h, tid & 63);
+    const uint32_t at = mh.at(p, n);
     // the partial outputs first (their loads are independent of the weights)
     float v[kMergeBatch];
 #pragma unroll
     for (int u = 0; u < kMergeBatch; ++u)
-        v[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(mh.rsrc, mh.at(p, u, n), 0, 0));
+        v[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(mh.rsrc, at + uint32_t(u) * mh.o_step, 0, 0));
     const float2 wd = merge_weights(mh.m_l);
     float acc = 0.f;
     for (int s0 = 0; s0 < p.nsp; s0 += kMergeBatch) {
         if (s0 > 0) {
 #pragma unroll
             for (int u = 0; u < kMergeBatch; ++u)
-                v[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(mh.rsrc, mh.at(p, s0 + u, n), 0, 0));
+                v[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(mh.rsrc, at + uint32_t(s0 + u) * mh.o_step, 0, 0));
         }
 #pragma unroll
         for (int u = 0; u < kMergeBatch; ++u) acc = __builtin_fmaf(weight_of(wd.x, s0 + u), v[u], acc);
@@ -663,17 +667,18 @@ __device__ __forceinline__ void merge_block_wide(const AttnParams& p, int blk) {
     const int c = (blk - h * n_cb) * 4 * kMergeWideThreads + 4 * tid;
     MergeHead mh;
     mh.init(p, h, tid & 63);
+    const uint32_t at = mh.at(p, c);
     f32x4 v[BATCH];
 #pragma unroll
     for (int u = 0; u < BATCH; ++u)
-        v[u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(mh.rsrc, mh.at(p, u, c), 0, 0));
+        v[u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(mh.rsrc, at + uint32_t(u) * mh.o_step, 0, 0));
     const float2 wd = merge_weights(mh.m_l);
     f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
     for (int s0 = 0; s0 < p.nsp; s0 += BATCH) {
         if (s0 > 0) {
 #pragma unroll
             for (int u = 0; u < BATCH; ++u)
-                v[u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(mh.rsrc, mh.at(p, s0 + u, c), 0, 0));
+                v[u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(mh.rsrc, at + uint32_t(s0 + u) * mh.o_step, 0, 0));
         }
 #pragma unroll
         for (int u = 0; u < BATCH; ++u) {
@@ -704,6 +709,7 @@ struct AttnLaunch {
     int64_t grid = 0;
     int64_t merge_grid = 0;
     int variant = 0;
+    bool touch = false;   // long spans: chunks ahead are brought into L2
     int vsplit = 1;    // workgroups per (head block, span), each taking 1 / vsplit of d_v's columns (1, 2, 4)
 };
 
