@@ -190,8 +190,17 @@ class Workspace:
     def __init__(self, device=None):
         self.device = torch.device("cuda", torch.cuda.current_device()) if device is None else torch.device(device)
         self.buf = None
-        self.held = (0, 0)               # (pointer, bytes) of buf, replaced as one
         self._retired = []
+
+    @property
+    def buf(self) -> torch.Tensor | None:
+        return self._buf
+
+    @buf.setter
+    def buf(self, t: torch.Tensor | None) -> None:
+        # what calls launch with, (pointer, bytes), replaced as one and never that of a buffer given up
+        self.held = (0, 0) if t is None else (t.data_ptr(), t.numel())
+        self._buf = t
 
     def get(self, nbytes: int, stream=None) -> tuple[int, int]:
         if nbytes == 0:
@@ -205,7 +214,6 @@ class Workspace:
             if self.buf is not None:
                 self._retired.append(self.buf)
             self.buf = buf
-            self.held = (buf.data_ptr(), size)
         return self.held
 
 

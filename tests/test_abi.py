@@ -7,6 +7,7 @@ import os
 import re
 
 import pytest
+import torch
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HEADER = os.path.join(ROOT, "include", "nmm.h")
@@ -119,6 +120,18 @@ def test_matrix_core_plans_fit_the_library_scratch(M):
         for K in (64, 2047, 2048, 3072, 7168, 65536):
             for N in {128 * panels // blocks, max(1, 128 * panels // blocks - 127)}:
                 assert L.nmm_gemv_workspace_size(M, K, N, nmm.NMM_BF16, nmm.NMM_PATH_AUTO) <= nmm.NMM_NOALLOC_SCRATCH_BYTES, (K, N)
+
+
+def test_a_workspace_holds_the_buffer_it_has():
+    """Calls launch with the workspace's (pointer, bytes) pair: it follows the buffer, also where a program
+    replaces or drops it."""
+    ws = nmm.Workspace("cpu")
+    assert ws.held == (0, 0)
+    for n in (1 << 20, 256):
+        ws.buf = torch.zeros(n, dtype=torch.uint8)
+        assert ws.held == (ws.buf.data_ptr(), n)
+    ws.buf = None
+    assert ws.held == (0, 0) and ws.buf is None
 
 
 def test_workspace_init_validates():
