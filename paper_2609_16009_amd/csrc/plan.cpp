@@ -443,7 +443,7 @@ bool plan_mfma_nt(const GemvArgs& a, NtMfmaPlan* p) {
     const int64_t stride = int64_t(16) * q.nt * a.ldw * 2;
     q.rot = stride % (1 << 19) == 0 ? 1 : stride % (1 << 18) == 0 ? 2 : 0;
     q.grid = rup(q.row_blocks, 8) * q.mblocks;
-    if (q.grid >= kLimit) return false;
+    if (q.grid > int64_t(0xFFFFFFFF) / kThreads) return false;   // a launch has fewer than 2^32 threads
     *p = q;
     return true;
 }

@@ -52,6 +52,40 @@ static void check_nt(int64_t M, int64_t K, int64_t N) {
     EXPECT(q.grid == int64_t(q.mblocks) * q.row_blocks * q.ks);
 }
 
+// The matrix-core form: every row of Wt and of x in one block, a launchable grid, and only the tile shapes
+// mfma_nt.hip has kernels for.
+static void check_mfma_nt(int64_t M, int64_t K, int64_t N, int64_t ldx, int64_t ldw) {
+    GemvArgs a;
+    a.M = M; a.K = K; a.N = N; a.dt = NMM_BF16; a.ldx = ldx; a.ldw = ldw; a.ldy = N;
+    NtMfmaPlan q;
+    if (!plan_mfma_nt(a, &q)) {
+        EXPECT(M < 1 || K < 1 || N < 1 || (M == 1 && K > kMfmaNtOneRowK) || M * N >= int64_t(1) << 28);
+        return;
+    }
+    ++checked;
+    EXPECT(q.xr == 1 || q.xr == 2 || q.xr == 4 || q.xr == 8);
+    EXPECT(q.nt == 1 || (q.nt == 2 && q.xr >= 4));
+    EXPECT(q.depth == 2 || (q.depth == 3 && q.nt == 1 && q.xr < 4));
+    EXPECT(int64_t(q.mblocks) * 4 * q.xr >= M && int64_t(q.mblocks - 1) * 4 * q.xr < M);
+    EXPECT(int64_t(q.row_blocks) * 16 * q.nt >= N && int64_t(q.row_blocks - 1) * 16 * q.nt < N);
+    EXPECT(q.grid == (q.row_blocks + 7) / 8 * 8 * int64_t(q.mblocks));
+    EXPECT(q.grid * kThreads < int64_t(1) << 32);
+    EXPECT(q.rot >= 0 && q.rot <= 2);
+    const int64_t rows = M < 4 * q.xr ? M : 4 * q.xr;
+    EXPECT(q.xr == 1 || ((rows - 1) * ldx + (K + 7) / 8 * 8) * 2 < int64_t(1) << 31);
+}
+
+// A batch the matrix cores take: a launchable grid of 64-column panels and blocks of 16 rows or 32.
+static void check_heads(int64_t batch, int64_t M, int64_t K, int64_t N) {
+    if (!heads_on_mfma(batch, M, K, N)) {
+        EXPECT(batch <= 1 || M < 2 || K < 1 || N < 1 || K > kMfmaLongK || batch * N * M >= int64_t(1) << 30);
+        return;
+    }
+    ++checked;
+    EXPECT(batch > 1 && M >= 1 && K >= 1 && N >= 1 && (M > 1 || K <= 256));
+    EXPECT(batch * ((N + kHeadsCols - 1) / kHeadsCols) * ((M + 15) / 16) * kThreads < int64_t(1) << 31);
+}
+
 int main() {
     const int64_t Ms[] = {0, 1, 2, 3, 4, 5, 8, 9, 16, 17, 32, 33, 100};
     const int64_t Ks[] = {0, 1, 7, 8, 13, 513, 1536, 4099, 7168, 16384, 33000};
@@ -66,7 +100,18 @@ int main() {
                             check_gemv(b, m, k, n, dt, path);
     for (int64_t m : Ms)
         for (int64_t k : Ks)
-            for (int64_t n : Ns) check_nt(m, k, n);
+            for (int64_t n : Ns) {
+                check_nt(m, k, n);
+                for (int64_t pad : {0, 1}) check_mfma_nt(m, k, n, (k + 7) / 8 * 8 + 64 * pad, (k + 7) / 8 * 8 + 8 * pad);
+                for (int64_t b : Bs) check_heads(b, m, k, n);
+            }
+    check_mfma_nt(32, 8192, 8192, 8192, 8192);                      // row blocks 512 KB apart
+    check_mfma_nt(32, 8, 64, (int64_t(1) << 31) - 8, 8);            // x rows too far apart for 32 in a block
+    check_mfma_nt(1 << 14, 8, 1 << 20, 8, 8);                       // 2^24 workgroups
+    check_mfma_nt((1 << 14) - 32, 8, 1 << 20, 8, 8);                // the last size below
+    check_mfma_nt((int64_t(1) << 31) - 1, 8, (1 << 27) - 8, 8, 8);
+    check_heads(3, 1 << 20, 64, 1 << 15);
+    check_heads((int64_t(1) << 31) - 1, 2, 8, 8);
     // argument checks on the limits, and invalid arguments
     GemvPlan p;
     EXPECT(plan_gemv(1, 1, int64_t(1) << 31, 8, NMM_BF16, NMM_PATH_AUTO, &p) == NMM_ERR_SHAPE);
