@@ -3,6 +3,10 @@ every shape the GPU tests use: every W load must stay inside the W extent, every
 x, every LDS access inside the launch's dynamic LDS, and every y / partial-sum / ticket access
 inside its buffer.  This is the check that a launch cannot fault before it runs on a GPU.
 """
+import ctypes
+import os
+import subprocess
+
 import numpy as np
 import pytest
 
@@ -10,6 +14,25 @@ nmm = pytest.importorskip("paper_2609_16009_amd")
 import synthetic as syn  # noqa: E402
 
 WAVES, THREADS = 4, 256
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def planner(tmp_path_factory):
+    """csrc/plan.cpp behind tests/sanitize/plan_shim.cpp: the partitions that the ABI does not report."""
+    so = str(tmp_path_factory.mktemp("plan") / "plan.so")
+    csrc = os.path.join(ROOT, "paper_2609_16009_amd", "csrc")
+    r = subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", f"-I{os.path.join(ROOT, 'include')}", f"-I{csrc}",
+                        os.path.join(csrc, "plan.cpp"), os.path.join(ROOT, "tests", "sanitize", "plan_shim.cpp"), "-o", so],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    return ctypes.CDLL(so)
+
+
+def plan_of(fn, n, *sizes):
+    """The n values a planner call fills in, and what it returns."""
+    out = (ctypes.c_int64 * n)()
+    return fn(*map(ctypes.c_int64, sizes), out), list(out)
 
 
 def check_launch(batch, M, K, N, ldx, ldw, ldy, sx=None, sw=None, sy=None):
@@ -227,89 +250,76 @@ def test_kv_update_launch_stays_in_bounds(hidden, kv, rope, ldw):
 
 
 
-NT_SHAPES = [  # M, K, N, ldx, ldwt
-    (1, 16384, 7168, 16384, 16384), (1, 7168, 2112, 7168, 7168), (1, 1536, 24576, 1536, 1536),
-    (1, 1021, 1031, 1024, 1024), (1, 13, 8, 16, 16), (2, 20000, 40, 20000, 20000), (3, 4099, 520, 4104, 4104),
-    (4, 9000, 4200, 9000, 9000), (5, 777, 300, 784, 784), (16, 1536, 3000, 1536, 1536), (1, 1, 1, 8, 8),
-    (1, 100000, 64, 100000, 100000),
-    (1, 16383, 65521, 65528, 16384),      # Wt's extent 2^31 - 491,520 bytes: the largest offsets
+NT_SHAPES = [  # K, N, ldwt
+    (16384, 7168, 16384), (7168, 2112, 7168), (1536, 24576, 1536), (1021, 1031, 1024), (13, 8, 16), (20000, 40, 20000),
+    (4099, 520, 4104), (9000, 4200, 9000), (777, 300, 784), (1, 1, 8), (100000, 64, 100000),
+    (16383, 65521, 16384),      # Wt's extent 2^31 - 491,520 bytes: the largest offsets
 ]
 
 
-@pytest.mark.parametrize("M,K,N,ldx,ldwt", NT_SHAPES)
-def test_gemv_nt_launch_stays_in_bounds(M, K, N, ldx, ldwt):
-    """The transposed-weight GEMV (gemv_nt_kernel): every Wt load inside Wt's extent, x's staged
-    slice (16-bit) inside the 32 KB staging limit and the launch's LDS, every LDS read of x inside it,
-    partial sums and tickets inside the workspace, y writes inside y."""
-    import ctypes
-    L = nmm.lib()
-    mt = 1 if M <= 1 else 2 if M <= 2 else 4
-    mblocks = -(-M // mt)
-    slice_max = 16384 // mt
-    ks = -(-K // slice_max)
-    slice_k = -(-(-(-K // ks)) // 512) * 512
-    ks = -(-K // slice_k)
-    target_rb = max(1, 256 // (ks * mblocks))
-    r = min(8, max(1, N // (4 * target_rb)))
-    rg = 1 if r < 2 else 2 if mt == 1 else 4
-    r = -(-r // rg) * rg
+@pytest.mark.parametrize("K,N,ldwt", NT_SHAPES)
+def test_gemv_nt_launch_stays_in_bounds(planner, K, N, ldwt):
+    """The streaming transposed-weight GEMV of one row (gemv_nt_kernel; the planner's partition): every Wt load
+    inside Wt's extent and every row loaded once, x's staged slice (16-bit) inside the 32 KB staging limit and
+    the launch's LDS, every LDS read of x inside it, partial sums and tickets inside the workspace."""
+    st, (r, row_blocks, rg, slice_k, ks, grid, tickets, ws) = plan_of(planner.plan_nt, 8, 1, K, N)
+    assert st == nmm.NMM_OK and ws == nmm.lib().nmm_gemv_nt_workspace_size(1, K, N, nmm.NMM_BF16)
+    assert rg in (1, 2) and r % rg == 0 and slice_k % 512 == 0 and (ks - 1) * slice_k < K <= ks * slice_k
     R = 4 * r
-    row_blocks = -(-N // R)
-    grid = mblocks * row_blocks * ks
-    ws = L.nmm_gemv_nt_workspace_size(M, K, N, nmm.NMM_BF16)
+    assert (row_blocks - 1) * R < N <= row_blocks * R and grid == row_blocks * ks < 2 ** 24
     if ks > 1:
-        assert ws == 64 * 1024 + grid * mt * R * 4 and mblocks * row_blocks <= 16384
+        assert ws == 64 * 1024 + grid * R * 4 and tickets == row_blocks <= 16384
     else:
         assert ws == 0
     extent = ((N - 1) * ldwt + (K + 7) // 8 * 8) * 2
-    lds_halves = slice_k * mt
+    assert extent < 2 ** 31
     lane = np.arange(64)
-    part_floats = grid * mt * R
     for sl in sorted({0, ks - 1}):
         k0 = sl * slice_k
         klen = min(slice_k, K - k0)
         J = -(-klen // 512)
-        assert J * 512 * mt <= 16384 and J * 512 * mt <= lds_halves         # staged x fits
+        assert J * 512 <= slice_k <= 16384                                  # staged x fits
         for rb in sorted({0, row_blocks - 1}):
-            for wave in range(4):
-                row0 = rb * R + wave * r
-                for i in range(r):
-                    n = row0 + i
-                    for j in range(J):
-                        k = k0 + j * 512 + 8 * lane
-                        issued = (n < N) & (k < K)
-                        off = n * ldwt * 2 + k * 2
-                        assert np.all(off[issued] + 16 <= extent)
-                        kb = j * 512 + 8 * lane
-                        assert np.all((kb + 7) * mt + mt - 1 < lds_halves)   # LDS reads of x
-                    if ks > 1:
-                        for mb in range(mblocks):
-                            pbase = ((mb * row_blocks + rb) * ks + sl) * mt * R
-                            assert pbase + (mt - 1) * R + wave * r + i < part_floats
+            rows = [rb * R + wave * r + g * rg + i for wave in range(4) for g in range(r // rg) for i in range(rg)]
+            assert rows == list(range(rb * R, rb * R + R))
+            for n in rows:
+                for j in range(J):
+                    k = k0 + j * 512 + 8 * lane
+                    issued = (n < N) & (k < K)
+                    off = n * ldwt * 2 + k * 2
+                    assert np.all(off[issued] + 16 <= extent)
+                if ks > 1:
+                    assert 64 * 1024 + ((rb * ks + sl) * R + n - rb * R) * 4 + 4 <= ws
 
 
 @pytest.mark.parametrize("M,K,N,ldx,ldwt", [(2, 13, 8, 16, 16), (5, 777, 300, 784, 800), (16, 4099, 5003, 4104, 4104),
                                             (33, 1000, 4900, 1000, 1000), (1, 2048, 47, 2048, 2048), (4, 129, 33, 136, 136),
+                                            (16, 16384, 7168, 16384, 16384), (8, 8192, 4097, 8192, 8192),
                                             (32, 128, 16, 128, 128), (16, 16383, 65521, 16384, 16384)])
-def test_mfma_nt_launch_covers_every_chunk_in_bounds(M, K, N, ldx, ldwt):
-    """mfma_nt_kernel: a wave's LDS-direct loads (4 rows x 16 chunks each, chunk c of row r in slot
-    c ^ (r % 16)) take every 16-byte chunk of a workgroup's rows of Wt and x exactly once, whatever the
-    round the block starts at, inside both extents; and every fragment read finds row j's chunk
-    4 s + g of its group."""
-    xr = 1 if M <= 4 else 2 if M <= 8 else 4 if M <= 16 else 8
-    nt = 2 if xr >= 4 and -(-N // 32) >= 150 else 1
-    stride = 16 * nt * ldwt * 2
-    rot = 1 if stride % (1 << 19) == 0 else 2 if stride % (1 << 18) == 0 else 0
+def test_mfma_nt_launch_covers_every_chunk_in_bounds(planner, M, K, N, ldx, ldwt):
+    """mfma_nt_kernel on the planner's partition: every (row block, block of x) once in the grid; a wave's
+    LDS-direct loads (4 rows x 16 chunks each, chunk c of row r in slot c ^ (r % 16)) take every 16-byte chunk
+    of a workgroup's rows of Wt and x exactly once, whatever the round the block starts at, inside both extents;
+    and every fragment read finds row j's chunk 4 s + g of its group."""
+    taken, (xr, mblocks, nt, depth, rot, row_blocks, grid) = plan_of(planner.plan_nt_matrix_cores, 7, M, K, N, ldx, ldwt)
+    assert taken and (xr, nt, depth) in {(1, 1, 2), (1, 1, 3), (2, 1, 2), (2, 1, 3), (4, 1, 2), (4, 2, 2), (8, 1, 2),
+                                         (8, 2, 2)}, "a form mfma_nt.hip has no kernel for"
     NW, group = 4, 128
     groups = -(-K // group)
     rounds = -(-groups // NW)
-    row_blocks, mblocks = -(-N // (16 * nt)), -(-M // (4 * xr))
+    assert 4 * xr * (mblocks - 1) < M <= 4 * xr * mblocks and 16 * nt * (row_blocks - 1) < N <= 16 * nt * row_blocks
+    bid = np.arange(grid)
+    rb_of, mb_of = (bid & 7) + 8 * (bid // (8 * mblocks)), (bid >> 3) % mblocks
+    pairs = list(zip(rb_of[rb_of < row_blocks], mb_of[rb_of < row_blocks]))
+    assert len(pairs) == row_blocks * mblocks == len(set(pairs))
     lane = np.arange(64)
     for rb in sorted({0, row_blocks // 2, row_blocks - 1}):
         start = rb * rot % rounds
         seq = [wave + (r + start - (rounds if r + start >= rounds else 0)) * NW for r in range(rounds) for wave in range(NW)]
         assert sorted(g for g in seq if g < groups) == list(range(groups))      # every group once
-        for rows, total, ld in ((16 * nt, N - rb * 16 * nt, ldwt), (4 * xr, M - (mblocks - 1) * 4 * xr, ldx)):
+        # Wt's offsets count from its first row, x's from its block's
+        for first, rows, total, ld in ((rb * 16 * nt, 16 * nt, N - rb * 16 * nt, ldwt),
+                                       (0, 4 * xr, M - (mblocks - 1) * 4 * xr, ldx)):
             seen = np.zeros((rows, 16), int)
             for q in range(rows // 4):
                 r, c = 4 * q + lane // 16, (lane % 16) ^ ((4 * q + lane // 16) & 15)
@@ -317,7 +327,6 @@ def test_mfma_nt_launch_covers_every_chunk_in_bounds(M, K, N, ldx, ldwt):
                 for g in (0, groups - 1):
                     k = g * group + 8 * c
                     ok = (r < total) & (k < K)
-                    first = rb * 16 * nt if ld == ldwt and rows == 16 * nt else 0
                     off = (first + r) * ld * 2 + 2 * k
                     extent = ((first + total - 1) * ld + (K + 7) // 8 * 8) * 2
                     assert np.all(off[ok] + 16 <= extent) and extent < 2 ** 31
@@ -336,11 +345,12 @@ def test_mfma_nt_launch_covers_every_chunk_in_bounds(M, K, N, ldx, ldwt):
 
 @pytest.mark.parametrize("M,K,N,ldx,ldw", [(4, 128, 512, 128, 512), (1, 1, 1, 8, 8), (17, 129, 65, 136, 72),
                                            (33, 513, 700, 520, 704), (2, 2048, 9, 2048, 16)])
-def test_mfma_heads_launch_covers_every_chunk_in_bounds(M, K, N, ldx, ldw):
-    """mfma_heads_kernel: a wave's LDS-direct loads take every 16-byte chunk of a workgroup's 64 columns
+def test_mfma_heads_launch_covers_every_chunk_in_bounds(planner, M, K, N, ldx, ldw):
+    """mfma_heads_kernel (the planner gives it batches of these sizes): a wave's LDS-direct loads take every 16-byte chunk of a workgroup's 64 columns
     of W (8 rows x 8 chunks a load) and of its x tile (16 rows x 4 chunks) exactly once and inside both
     extents, and every fragment read finds its chunk: W row 8 g + j / 4 (+ 4), columns 16 t + 4 (j % 4),
     and x row j, chunk g."""
+    assert planner.heads_take_matrix_cores(*map(ctypes.c_int64, (8, M, K, N)))
     lane = np.arange(64)
     g, j = lane >> 4, lane & 15
     f = lambda r: 2 * (((r >> 1) & 1) + 2 * ((r >> 3) & 1))
@@ -390,49 +400,37 @@ def test_random_batched_shapes_stay_in_bounds(case):
 
 
 @pytest.mark.parametrize("case", syn.random_nt_shapes(), ids=lambda c: f"{c[0]}x{c[1]}x{c[2]}")
-def test_random_nt_shapes_stay_in_bounds(case):
-    """The seeded sweep of the transposed-weight GEMV the GPU tests run (synthetic.random_nt_shapes)."""
+def test_random_nt_shapes_stay_in_bounds(planner, case):
+    """The seeded sweep of the transposed-weight product the GPU tests run (synthetic.random_nt_shapes), through
+    the model of the path each call takes."""
     M, K, N, dt, ldx, ldwt = case
-    test_gemv_nt_launch_stays_in_bounds(M, K, N, ldx, ldwt)
+    taken, _ = plan_of(planner.plan_nt_matrix_cores, 7, M, K, N, ldx, ldwt)
+    if taken:
+        test_mfma_nt_launch_covers_every_chunk_in_bounds(planner, M, K, N, ldx, ldwt)
+    else:
+        assert M == 1
+        test_gemv_nt_launch_stays_in_bounds(planner, K, N, ldwt)
 
 
 @pytest.mark.parametrize("heads,nope,rope,kv,ldq", [(128, 128, 64, 512, 576), (6, 40, 24, 136, 160), (4, 16, 8, 24, 40),
-                                                    (3, 8, 512, 8, 520), (1, 8, 2, 8, 10), (7, 16, 0, 8, 8)])
-def test_qrope_workgroup_covers_each_pair_once(heads, nope, rope, kv, ldq):
-    """The extra workgroup of the query launch (gemv_qrope_kernel): thread t takes pair
-    t % (rope/2) of heads t / (rope/2), t / (rope/2) + 256 / (rope/2), ...; every (head, pair) is
-    written exactly once, reads stay inside q [heads, nope + rope] and writes inside
-    q_out[h * ldq + kv .. kv + rope)."""
-    pairs = rope // 2
-    if pairs == 0:
-        return
-    qk = nope + rope
-    seen = np.zeros((heads, pairs), int)
-    hstep = THREADS // pairs
-    for t in range(THREADS):
-        j, h0 = t % pairs, t // pairs
-        if h0 >= hstep:
-            continue
-        for h in range(h0, heads, hstep):
-            seen[h, j] += 1
-            assert h * qk + nope + 2 * j + 1 < heads * qk
-            assert kv + 2 * j + 1 < ldq and h * ldq + kv + 2 * j + 1 < heads * ldq
-    assert np.all(seen == 1)
-
-
-@pytest.mark.parametrize("heads,rope", [(128, 64), (6, 24), (4, 8), (3, 512), (1, 2), (7, 0), (33, 64)])
-def test_qrope_threads_cover_each_pair_once(heads, rope):
-    """The extra workgroups of the query launch, one (head, pair) per thread: ceil(heads rope / 2 / 256)
-    of them (none without a rope part) write every pair of every head exactly once."""
-    pairs = rope // 2
+                                                    (3, 8, 512, 8, 520), (1, 8, 2, 8, 10), (7, 16, 0, 8, 8),
+                                                    (33, 128, 64, 512, 576)])
+def test_qrope_threads_cover_each_pair_once(heads, nope, rope, kv, ldq):
+    """The extra workgroups of the query launch (gemv_qrope_kernel), one (head, pair) per thread:
+    ceil(heads rope / 2 / 256) of them (none without a rope part) write every pair of every head exactly once,
+    read inside q [heads, nope + rope] and write inside q_out[h * ldq + kv .. kv + rope)."""
+    pairs, qk = rope // 2, nope + rope
     t = np.arange(-(-heads * pairs // THREADS) * THREADS)
     if pairs == 0:
         assert t.size == 0
         return
     h, j = t // pairs, t % pairs
+    h, j = h[h < heads], j[h < heads]
     seen = np.zeros((heads, pairs), int)
-    np.add.at(seen, (h[h < heads], j[h < heads]), 1)
+    np.add.at(seen, (h, j), 1)
     assert np.all(seen == 1)
+    assert np.all(h * qk + nope + 2 * j + 1 < heads * qk)
+    assert np.all(kv + 2 * j + 1 < ldq) and np.all(h * ldq + kv + 2 * j + 1 < heads * ldq)
 
 
 def default_spans(heads, seq):
