@@ -91,6 +91,15 @@ def test_nt_matrix_core_edges_integer_exact(M, K, N, ldwt):
         check_nt(c, ldwt, ldy=N + 3)
 
 
+@pytest.mark.parametrize("dt", [syn.BF16, syn.F16])
+@pytest.mark.parametrize("K,N", [(2049, 33), (2055, 2500), (2056, 2500), (16385, 2049), (20000, 5003)])
+def test_nt_one_row_streams_integer_exact(K, N, dt):
+    # one row past the matrix cores' K: one and two rows of Wt a step, K inside a 16-byte chunk and on its edge, one
+    # slice and two; NaN past K must not reach a sum
+    c = syn.gemv_case(950 + K % 89, 1, K, N, dt, integer=True, ldx=(K + 7) // 8 * 8, name=f"nt_stream_{K}x{N}")
+    check_nt(c, (K + 7) // 8 * 8 + 8, ldy=N + 3)
+
+
 def test_nt_matrix_cores_keep_subnormals():
     # fp16 subnormal inputs, and bf16 products below the fp32 normal range, are exact
     for dt, a, b in ((torch.float16, 2.0 ** -24, 1.0), (torch.bfloat16, 2.0 ** -70, 2.0 ** -70)):
