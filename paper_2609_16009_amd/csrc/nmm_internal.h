@@ -39,7 +39,9 @@ constexpr int kMfmaStageRows = 64;
 constexpr int kHeadsCols = 64;             // columns per workgroup of the batched matrix-core kernel
 constexpr int kMfmaTargetGrid = 256;      // the matrix-core plan splits K while the grid stays within this
 constexpr int64_t kMfmaShortK = 3072;
-constexpr int64_t kMfmaLongK = 2048;
+constexpr int64_t kMfmaLongK = 2048;      // K from which a 16-row tile takes three slices over 129 to 170 panels
+constexpr int64_t kMfmaLongK32 = 2560;    // and a 32-row tile
+constexpr int64_t kHeadsLongK = 2048;     // a batch's K past which the matrix cores need 256 workgroups
 constexpr int kMfmaMinMDefault = 3;        // AUTO uses the matrix cores from this many rows on
 
 struct GemvPlan {

@@ -161,12 +161,15 @@ nmm_status plan_mfma(int64_t M, int64_t K, int64_t N, GemvPlan* p) {
     // a short K takes at most 8 slices ([1536, 1536] 6.6 us, 12 slices 6.8; [512, 512] 5.1, 2 slices 6.3)
     const int64_t ks_cap = tuned("NMM_GEMV_MAXSPLIT", K < kMfmaShortK ? 8 : 16);
     int64_t ks_want = std::max<int64_t>(1, want / panels);
-    // fewer than 70 % of the CUs in use on a long K: two workgroups per CU, which still fit side by side
-    // ([4096, 16640], 130 panels: 28.3 us with 3 slices against 33.8 with one; on K = 1024 11.3 against 10.1)
-    if (ks_want * panels * 10 < want * 7 && K >= kMfmaLongK) ks_want = std::max(ks_want, 2 * want / panels);
-    // nor more slices than nmm_gemv_noalloc's scratch holds (170 panels of 32 rows: two, not three)
+    // no more slices than nmm_gemv_noalloc's scratch holds (170 panels of 32 rows: two)
     const int64_t slice_bytes = panels * q.mt * kMfmaPanelCols * 4;
     const int64_t fits = (int64_t(NMM_NOALLOC_SCRATCH_BYTES) - kTicketBytes) / slice_bytes;
+    // 129 to 170 panels on a long K: three slices, two workgroups per CU side by side.  At 4 / 32 rows [4096, 16512]
+    // 26.6 / 30.5 us against 29.2 / 31.0 with one, [2560, 20480] 20.8 / 23.6 against 22.5 / 25.0, [2048, 16512] 16.1 /
+    // 19.3 against 16.4 / 17.8; two slices lose to one wherever the grid has over 128 panels ([2048, 22400], 175 panels,
+    // 20.4 / 23.4 against 18.2 / 19.9; [4096, 16512] 32.2 / 38.4), and five to two at 86 to 89 ([2048, 11136] 13.0 / 16.2
+    // against 12.0 / 14.3)
+    if (ks_want == 1 && 2 * want / panels == 3 && fits >= 3 && K >= (q.mt == 16 ? kMfmaLongK : kMfmaLongK32)) ks_want = 3;
     ks_want = std::max<int64_t>(1, std::min(std::min(ks_want, ks_cap), fits));
     int64_t r = rup(cdiv(K, ks_want), kMfmaStageRows);
     int64_t k = cdiv(K, r);
@@ -341,7 +344,7 @@ bool heads_on_mfma(int64_t batch, int64_t M, int64_t K, int64_t N) {
     const int64_t groups = batch * cdiv(N, kHeadsCols);          // workgroups per row block
     if (groups * cdiv(M, 16) >= kLimit / kThreads) return false;
     if (M == 1) return K <= 256 && groups <= 512;
-    return K <= kMfmaLongK || groups >= 256;
+    return K <= kHeadsLongK || groups >= 256;
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -78,7 +78,7 @@ static void check_mfma_nt(int64_t M, int64_t K, int64_t N, int64_t ldx, int64_t 
 // A batch the matrix cores take: a launchable grid of 64-column panels and blocks of 16 rows or 32.
 static void check_heads(int64_t batch, int64_t M, int64_t K, int64_t N) {
     if (!heads_on_mfma(batch, M, K, N)) {
-        EXPECT(batch <= 1 || M < 2 || K < 1 || N < 1 || K > kMfmaLongK || batch * N * M >= int64_t(1) << 30);
+        EXPECT(batch <= 1 || M < 2 || K < 1 || N < 1 || K > kHeadsLongK || batch * N * M >= int64_t(1) << 30);
         return;
     }
     ++checked;

@@ -174,6 +174,17 @@ def test_plan_covers_w_exactly_once(M, K, N, batch):
     assert nmm.nmm_batched_gemv_workspace_size(batch, M, K, N, nmm.NMM_BF16, nmm.NMM_PATH_GEMV) == p["workspace_bytes"]
 
 
+@pytest.mark.parametrize("M,long_k", [(4, 2048), (16, 2048), (17, 2560), (32, 2560)])
+def test_matrix_core_slices_between_one_and_two_rounds(M, long_k):
+    """As many K-slices as keep one workgroup per CU, so two at 86 to 89 panels; at 129 to 170 panels three where K
+    is long (two workgroups per CU) and the library's scratch holds them, and one past that, never two."""
+    for K in (512, 2047, 2048, 2559, 2560, 4096, 7168):
+        for panels in (86, 89, 128, 129, 150, 169, 170, 171, 179, 200, 256):
+            p = nmm.nmm_gemv_plan(M, K, 128 * panels, nmm.NMM_BF16, nmm.NMM_PATH_MFMA)
+            three = 129 <= panels <= (170 if M <= 16 else 169) and K >= long_k
+            assert p["split_k_full"] == (2 if panels <= 128 else 3 if three else 1), (K, panels)
+
+
 def test_plan_rejects_unavailable_path_and_bad_dtype():
     info = nmm.nmm_plan_info()
     assert L.nmm_gemv_plan(1, 1, 64, 64, 7, 0, ctypes.byref(info)) == nmm.NMM_ERR_DTYPE
