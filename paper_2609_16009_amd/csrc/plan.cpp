@@ -99,34 +99,40 @@ nmm_status validate_gemv(const GemvArgs& a, int path) {
 
 // Panels and K-slices of a single 1- or 2-row product of up to 100 MB: chunks per panel, slices and
 // row-steps in flight.  Measured on MI355X at one row over panels of 8 to 64 chunks, 4 to 16 steps and
-// grids of 64 to 512 (best of each against the choice before, 128-byte panels and a power-of-two split):
-//  * no K-split where 150 to 256 panels of some width cover the row: nothing is handed over (W_UQ [1536,
-//    24576] 192 panels 14.4 us, [1536, 12288] 10.3; [700, 20000] 157 panels 9.0 against 12.3);
+// grids of 64 to 512 (against 128-byte panels and the power-of-two split that larger weights take):
+//  * no K-split where 150 to 256 panels of some width cover the row (from 129 on for 16 and 32 chunks): nothing is
+//    handed over (W_UQ [1536, 24576] 192 panels 14.7 us, [1536, 12288] 10.5; [700, 20000] 157 panels 8.4 against
+//    12.7; [1536, 18432] 144 panels 14.2 against 16.5; [1280, 34000] 133 panels of 32 19.6, 266 of 16 22.8);
 //  * else panels of 16 chunks (256 bytes: whole lines, also where rows start inside one) and as many
-//    slices, up to 8, as keep one workgroup per CU: [3000, 3000] 8.4 against 10.5, [4099, 5003] 13.1
-//    against 15.2, [4096, 7168] 13.5 against 15.5, [8192, 4096] 14.9 against 16.6, [1536, 6144] 8.1
-//    against 9.1;
-//  * panels of 8 chunks where that would need more slices, whose gather is a serial tail ([7168, 2112] 7
-//    slices 9.3, 16 chunks and 14 slices 10.5; [7168, 576] 7.3 and 7.7);
-//  * no split of K up to 512 either ([512, 512] 4.0, two slices 5.4);
-//  * up to 12 MB about 144 workgroups, as the streams are short ([2048, 2048] 128 workgroups 6.6, 256
-//    6.8; [4096, 1024] 128 7.2), and at most 4 slices of the wider panels ([2048, 2048] with 8 7.1).
-// Eight row-steps in flight serve a split K as well as sixteen; a long unsplit stream keeps sixteen.
+//    slices, up to 8, as keep one workgroup per CU: [3000, 3000] 8.4 against 10.7, [4099, 5003] 11.8
+//    against 15.5, [4096, 7168] 13.5 against 15.3, [8192, 4096] 14.7 against 16.7, [1536, 6144] 8.2
+//    against 9.3;
+//  * panels of 8 chunks where that would need more slices, whose gather is a serial tail ([7168, 576] 14 slices of 9
+//    panels 7.0, of 5 wider ones 7.5; [7168, 2112] 7 slices 9.5, 14 of the wider panels 9.5);
+//  * no split of K up to 512 either ([512, 512] 4.5, two slices 5.0); rows past 256 panels of 32 chunks take 16, or
+//    64 where K has few steps or they fit one round ([512, 70000] 16.2 and 15.9, 8 chunks 17.0; [64, 80000] 64
+//    chunks 5.1, 8 chunks 8.5; [256, 131072] 64 chunks 12.5, 16 chunks 13.3, 8 chunks 15.7);
+//  * up to 12 MB about 144 workgroups, as the streams are short ([2048, 2048] 128 workgroups 6.8, 256
+//    6.8; [4096, 1024] 128 6.9, 8 chunks and 256 8.1), and at most 4 slices of the wider panels.
+// Eight row-steps in flight serve a split K and a short one as well as sixteen or better ([512, 8192] 4.9 and 5.2,
+// [64, 512] 3.2 and 3.7: at 8 chunks 16 steps are 512 rows).  A long unsplit stream keeps sixteen (W_UQ 14.7, eight
+// 15.5), panels of 32 chunks in fewer than 150 workgroups only for two rows ([1280, 36000] one row 19.1 with eight
+// and 20.7 with sixteen, two rows 23.1 and 19.9).
 struct NarrowChoice {
-    int cw = 0, ks = 1, unroll = 16;
+    int cw = 0, ks = 1, unroll = 8;
 };
-NarrowChoice narrow_plan(int64_t K, int64_t chunks, int64_t w_bytes) {
+NarrowChoice narrow_plan(int mt, int64_t K, int64_t chunks, int64_t w_bytes) {
     NarrowChoice c;
     for (int cw : {32, 16, 8}) {
         const int64_t panels = cdiv(chunks, cw);
-        if (panels >= 150 && panels <= 256) {
-            c.cw = cw;
-            c.unroll = K >= 1024 ? 16 : 8;
-            return c;
-        }
+        if (panels < (cw == 8 ? 150 : 129) || panels > 256) continue;
+        c.cw = cw;
+        if (panels >= 150 ? K >= 1024 : cw == 32 && mt == 2 && K > 512) c.unroll = 16;
+        return c;
     }
+    const int64_t widest = cdiv(chunks, kPanelChunks);
     if (K <= 512) {
-        c.cw = 8;
+        c.cw = cdiv(chunks, 32) <= 256 ? 8 : K < 128 || (widest > 200 && widest <= 256) ? kPanelChunks : 16;
         return c;
     }
     const bool small = w_bytes <= int64_t(12) << 20;
@@ -134,7 +140,6 @@ NarrowChoice narrow_plan(int64_t K, int64_t chunks, int64_t w_bytes) {
     const int64_t wide = want / cdiv(chunks, 16);
     c.cw = wide <= (small ? 4 : 10) ? 16 : 8;
     c.ks = static_cast<int>(std::max<int64_t>(1, c.cw == 16 ? std::min<int64_t>(8, wide) : std::min<int64_t>(16, want / cdiv(chunks, 8))));
-    c.unroll = 8;
     return c;
 }
 
@@ -230,7 +235,7 @@ nmm_status plan_gemv(int64_t batch, int64_t M, int64_t K, int64_t N, int dt, int
     // up to 512 columns with 8 row-steps in flight.  Taller tiles keep 4 in flight and more workgroups.
     const bool narrow_m = q.mt <= 2;
     const bool deep = narrow_m && w_bytes <= int64_t(100) << 20;
-    const NarrowChoice nc = deep && mats == 1 && K > 0 && N > 0 ? narrow_plan(K, chunks, w_bytes) : NarrowChoice{};
+    const NarrowChoice nc = deep && mats == 1 && K > 0 && N > 0 ? narrow_plan(q.mt, K, chunks, w_bytes) : NarrowChoice{};
     q.unroll = unroll > 0 ? unroll : static_cast<int>(tuned("NMM_GEMV_UNROLL", nc.cw ? nc.unroll : deep ? 16 : narrow_m ? 8 : 4));
     if (q.unroll != 2 && q.unroll != 4 && q.unroll != 8 && q.unroll != 16) q.unroll = 8;
     if (q.unroll == 16 && q.mt > 2) q.unroll = 8;                  // 16 only for 1- and 2-row tiles

@@ -249,6 +249,19 @@ def test_narrow_plans_integer_exact(M, K, N):
         assert torch.isnan(y[:, N:]).all()
 
 
+@pytest.mark.parametrize("M", [1, 2])
+@pytest.mark.parametrize("K,N", [(64, 66001), (65, 17000), (300, 70000), (200, 131000), (520, 33000), (800, 65600)])
+def test_wide_rows_integer_exact(M, K, N):
+    # panels of 64, 16, 16, 64, 32 and (two slices and a last panel of 8 chunks) 64 chunks, all off the tile edges
+    c = syn.gemv_case(K + N, M, K, N, syn.BF16, integer=True, ldx=(K + 7) // 8 * 8, ldw=(N + 7) // 8 * 8)
+    y_ref, a_ref = oracle.gemv(c.x, c.W, c.dt, K=K, N=N)
+    y = torch.full((M, N + 3), float("nan"), dtype=torch.float32, device="cuda")
+    nmm.nmm_gemv(dev16(c.x, c.dt), dev16(c.W, c.dt), y, N=N, path=nmm.NMM_PATH_GEMV)
+    torch.cuda.synchronize()
+    assert_parity(y[:, :N], y_ref, a_ref, integer=True, what=f"{M}x{K}x{N}")
+    assert torch.isnan(y[:, N:]).all(), "columns past N were written"
+
+
 def test_infinity_propagates_to_its_column_only():
     c = syn.gemv_case(6, 1, 3000, 700, syn.BF16, ldw=704)
     W = c.W.copy()

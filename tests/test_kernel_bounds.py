@@ -114,6 +114,8 @@ SHAPES = [  # batch, M, K, N, ldx, ldw
     (1, 2, 500, 70, 504, 72), (1, 1, 4000, 1000, 4000, 1000), (1, 1, 3000, 700, 3000, 704),
     (128, 1, 128, 512, 128, 512), (128, 1, 512, 128, 512, 128), (3, 2, 1000, 72, 1000, 72),
     (5, 16, 96, 1000, 96, 1000), (2, 1, 20000, 40, 20000, 40),
+    (1, 1, 64, 66001, 64, 66008), (1, 2, 300, 70000, 304, 70000), (1, 1, 200, 131000, 200, 131000),   # wide rows
+    (1, 2, 520, 33000, 520, 33000), (1, 1, 800, 65600, 800, 65600),
     (1, 1, 65521, 16383, 65528, 16384),   # W's extent 2^31 - 491,520 bytes: the largest offsets
 ]
 
