@@ -293,9 +293,15 @@ nmm_status plan_gemv(int64_t batch, int64_t M, int64_t K, int64_t N, int dt, int
         } else {
             while (ks_want < ks_cap && double(ks_want) * 1.41421356 < ratio) ks_want *= 2;   // nearest power of two
             ks_want = std::min(ks_want, ks_cap);
-            // one or two rows: not more than one workgroup per CU ([10000, 9001], 36 panels: 7 slices 31.4
-            // us, 8 slices 41.8)
-            if (narrow_m && mats == 1 && ks_want * panels_all > want) ks_want = std::max<int64_t>(1, want / panels_all);
+            // one or two rows: not more than one workgroup per CU ([10000, 9001], 36 panels: 7 slices 32.1
+            // us, 8 slices 42.0).  Where that leaves over 30 % of the CUs idle, a last panel of up to a quarter's width,
+            // whose workgroups end early, does not count ([800, 65600], 128 panels and 8 chunks: two slices 19.8,
+            // one 21.4; but [4096, 16512], 32 panels and 16 chunks: 7 slices 26.5, 8 slices 27.8)
+            if (narrow_m && mats == 1 && ks_want * panels_all > want) {
+                const int64_t fit = std::max<int64_t>(1, want / panels_all);
+                const bool idle = fit * panels_all * 10 < want * 7;
+                ks_want = idle && q.tail_chunks && 4 * q.tail_chunks <= q.cw_full ? std::max<int64_t>(1, want / q.n_full) : fit;
+            }
         }
     }
 

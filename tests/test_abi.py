@@ -201,6 +201,15 @@ def test_short_and_wide_one_and_two_row_plans(M):
         assert (p["panel_width"], p["split_k_full"], p["unroll"]) == (32, 1, 8 * M)
 
 
+@pytest.mark.parametrize("M,K,N,ks", [(1, 800, 65600, 2), (2, 2000, 65600, 2), (1, 1736, 66048, 1), (2, 4096, 16512, 7),
+                                      (1, 10000, 9001, 7), (1, 16384, 7168, 8)])
+def test_a_narrow_last_panel_does_not_halve_the_grid(M, K, N, ks):
+    """Weights over 100 MB at one and two rows: at most one workgroup per CU, but a last panel of a few chunks does not
+    count where it would cost the other panels a slice and leave the chip half idle."""
+    p = nmm.nmm_gemv_plan(M, K, N, nmm.NMM_BF16, nmm.NMM_PATH_GEMV)
+    assert p["split_k_full"] == ks and 2 * K * N > 100 << 20
+
+
 def test_plan_rejects_unavailable_path_and_bad_dtype():
     info = nmm.nmm_plan_info()
     assert L.nmm_gemv_plan(1, 1, 64, 64, 7, 0, ctypes.byref(info)) == nmm.NMM_ERR_DTYPE
