@@ -117,7 +117,8 @@ nmm_status validate_gemv(const GemvArgs& a, int path) {
 // Eight row-steps in flight serve a split K and a short one as well as sixteen or better ([512, 8192] 4.9 and 5.2,
 // [64, 512] 3.2 and 3.7: at 8 chunks 16 steps are 512 rows).  A long unsplit stream keeps sixteen (W_UQ 14.7, eight
 // 15.5), panels of 32 chunks in fewer than 150 workgroups only for two rows ([1280, 36000] one row 19.1 with eight
-// and 20.7 with sixteen, two rows 23.1 and 19.9).
+// and 20.7 with sixteen, two rows 23.1 and 19.9), which below K = 768 take twice the workgroups and four steps
+// instead ([260, 34000] 7.9 against 8.5, [520, 33280] 10.6 and 11.2).
 struct NarrowChoice {
     int cw = 0, ks = 1, unroll = 8;
 };
@@ -127,7 +128,12 @@ NarrowChoice narrow_plan(int mt, int64_t K, int64_t chunks, int64_t w_bytes) {
         const int64_t panels = cdiv(chunks, cw);
         if (panels < (cw == 8 ? 150 : 129) || panels > 256) continue;
         c.cw = cw;
-        if (panels >= 150 ? K >= 1024 : cw == 32 && mt == 2 && K > 512) c.unroll = 16;
+        if (panels >= 150) {
+            if (K >= 1024) c.unroll = 16;
+        } else if (cw == 32 && mt == 2) {
+            if (K < 768) c.cw = 16;
+            c.unroll = K < 768 ? 4 : 16;
+        }
         return c;
     }
     const int64_t widest = cdiv(chunks, kPanelChunks);
