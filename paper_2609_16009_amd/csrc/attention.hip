@@ -226,7 +226,9 @@ nmm_status prepare(int64_t heads, int64_t seq, int64_t d_qk, int64_t d_v, const 
     // buffer alone (one chunk per span in flight, 4.7 MB over 64 spans) cannot cover from HBM: with the
     // straight-line merge, 16 heads x 131072 positions 72.9 -> 56.7 us, 128 x 32768 28.4 -> 26.4, 128 x 65536
     // 39.5 -> 38.3.  Short spans gain nothing (four chunks: 13.0 either way), and beside a
-    // GEMV's stream the attention keeps its loads as they are.
+    // GEMV's stream the attention keeps its loads as they are.  Under 8 spans, whose workgroups are not grouped on one
+    // XCD, the touches are spread over more L2s and pay all the same (the cache cold, without / with: 128 heads x 16384
+    // positions in 4 spans 110.8 / 85.6, 16 x 4096 in 7 spans 23.8 / 22.3, 1024 x 3500 in 7 spans 26.6 / 25.2).
     out->touch = hbh == kAloneHeads && a.span >= kTouchMinChunks * kCh;
     p.scale_log2 = scale * 1.4426950408889634f;
     p.kv_extent = static_cast<uint32_t>(extent);

@@ -551,7 +551,8 @@ __device__ __forceinline__ void attention_block(const AttnParams p, int bid) {
 // Lane s of every wave loads span s's (m, l) (at most 64 spans), so M and the normaliser come from
 // one load and fixed-order butterflies; each thread loads its columns of every span at once (up to 64
 // in merge_block_wide, 32 in merge_block) and sums them in span order with explicit fused multiply-adds,
-// the weights taken from lane s.  A block waits for about one memory round trip.  Two forms, which give the same bits (the same
+// the weights taken from lane s.  A block waits for about one memory round trip
+// (merge_block for two past 32 spans).  Two forms, which give the same bits (the same
 // operations on every output, in the same order):
 //  * merge_block: block `blk` owns one head and 256 of its columns, one per thread `tid` (heads x
 //    ceil(d_v / 256) blocks of 256 threads): many light blocks, for the workgroups another

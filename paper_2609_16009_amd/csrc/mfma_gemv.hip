@@ -19,13 +19,14 @@
 //  * Wave w owns the column tiles 2w and 2w+1 of the panel, so no cross-wave reduction is needed.  W
 //    is the A operand and x the B operand, so a lane ends with 4 consecutive columns of one row and
 //    stores 16 bytes at a time.
-//  * Sums: the two MFMAs of a stage chain in fp32 from zero and are added in fp64; the K-slices are
-//    added in fp64 as well.  Relative 2-norm error 5e-8 at any K; one fp32 chain over K: 2.3e-7 at
-//    K = 1536, 8.0e-7 at 16384.
+//  * Sums: the two MFMAs of a stage (at 32 rows the four of two stages) chain in fp32 from zero and are
+//    added in fp64; the K-slices are added in fp64 as well.  Relative 2-norm error for K of 512 to 16384: up to 16
+//    rows 4.9e-8 to 5.7e-8 in bf16 and 6.2e-8 to 7.0e-8 in fp16, 32 rows 6.5e-8 to 7.0e-8 and 8.0e-8 to 8.6e-8; one
+//    fp32 chain over K: 2.3e-7 at K = 1536, 8.0e-7 at 16384.
 //  * K-slices are combined like the GEMV's: device-scope stores of the slice's M rows (not of the
 //    whole 16- or 32-row tile), a ticket per panel, and the last workgroup sums the slices in order,
-//    16 bytes a load.  The tail is what bounds short weights: [7168, 2112] at 3 rows 10.5 us (13.3
-//    with 4-byte partials of all 16 rows and 16 slices), [7168, 576] 8.0 (9.8).
+//    16 bytes a load.  The tail is what bounds short weights: [7168, 2112] at 3 rows 10.7 us (13.9
+//    with 4-byte partials of all 16 rows and 16 slices), [7168, 576] 7.8 (10.3).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

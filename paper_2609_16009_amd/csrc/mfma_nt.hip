@@ -16,10 +16,10 @@
 //  * Sums: a chain of two MFMAs in fp32, then added in fp64 (the vector units are idle), waves
 //    added in fp64 in wave order, one rounding to fp32 at the end.  One fp32 chain over K loses
 //    precision with its length (relative 2-norm error 2.3e-7 at K = 1536, 8.0e-7 at 16384, against
-//    7.1e-8 and 1.3e-7 for fp32 FMAs over 64 lanes); this form measures 4.9e-8 in bf16 and 6.3e-8
-//    in fp16, at any K.
-//  * Bound by the weight's bytes up to about 16 rows (W_O 41 to 43 us, 5.6 TB/s), then also by x from
-//    L2, which every workgroup reads whole: 48 us at 32.
+//    7.1e-8 and 1.3e-7 for fp32 FMAs over 64 lanes); this form measures 4.7e-8 to 5.1e-8 in bf16 and
+//    6.1e-8 to 6.6e-8 in fp16 for K of 512 to 16384.
+//  * Bound by the weight's bytes up to about 16 rows (W_O 40 to 44 us, 5.3 to 5.9 TB/s), then also by x from
+//    L2, which every workgroup reads whole: 47 us at 32.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -26,7 +26,7 @@ int next_pow2(int64_t v) {
 }
 
 // The partition's tuning constants are fixed in the library, so a plan (and with it the order of
-// every sum) depends on the shape alone.  Only a library built with -DNMM_TUNING_ENV, for tuning
+// every sum) depends on the sizes alone, and for an [N, K] weight on its leading dimensions too.  Only a library built with -DNMM_TUNING_ENV, for tuning
 // sweeps, lets the environment override them; the library as built for use reads no environment.
 int64_t tuned(const char* name, int64_t dflt) {
 #ifdef NMM_TUNING_ENV
@@ -101,24 +101,24 @@ nmm_status validate_gemv(const GemvArgs& a, int path) {
 // row-steps in flight.  Measured on MI355X at one row over panels of 8 to 64 chunks, 4 to 16 steps and
 // grids of 64 to 512 (against 128-byte panels and the power-of-two split that larger weights take):
 //  * no K-split where 150 to 256 panels of some width cover the row (from 129 on for 16 and 32 chunks): nothing is
-//    handed over (W_UQ [1536, 24576] 192 panels 14.7 us, [1536, 12288] 10.5; [700, 20000] 157 panels 8.4 against
-//    12.7; [1536, 18432] 144 panels 14.2 against 16.5; [1280, 34000] 133 panels of 32 19.6, 266 of 16 22.8);
+//    handed over (W_UQ [1536, 24576] 192 panels 14.5 us, [1536, 12288] 10.5; [700, 20000] 157 panels 8.7 against
+//    12.8; [1536, 18432] 144 panels 14.0 against 16.5; [1280, 34000] 133 panels of 32 21.5, 266 of 16 23.3);
 //  * else panels of 16 chunks (256 bytes: whole lines, also where rows start inside one) and as many
-//    slices, up to 8, as keep one workgroup per CU: [3000, 3000] 8.4 against 10.7, [4099, 5003] 11.8
-//    against 15.5, [4096, 7168] 13.5 against 15.3, [8192, 4096] 14.7 against 16.7, [1536, 6144] 8.2
-//    against 9.3;
+//    slices, up to 8, as keep one workgroup per CU: [3000, 3000] 8.5 against 11.1, [4099, 5003] 11.8
+//    against 15.6, [4096, 7168] 13.5 against 15.5, [8192, 4096] 14.7 against 16.8, [1536, 6144] 8.1
+//    against 9.4;
 //  * panels of 8 chunks where that would need more slices, whose gather is a serial tail ([7168, 576] 14 slices of 9
-//    panels 7.0, of 5 wider ones 7.5; [7168, 2112] 7 slices 9.5, 14 of the wider panels 9.5);
-//  * no split of K up to 512 either ([512, 512] 4.5, two slices 5.0); rows past 256 panels of 32 chunks take 16, or
-//    64 where K has few steps or they fit one round ([512, 70000] 16.2 and 15.9, 8 chunks 17.0; [64, 80000] 64
-//    chunks 5.1, 8 chunks 8.5; [256, 131072] 64 chunks 12.5, 16 chunks 13.3, 8 chunks 15.7);
-//  * up to 12 MB about 144 workgroups, as the streams are short ([2048, 2048] 128 workgroups 6.8, 256
-//    6.8; [4096, 1024] 128 6.9, 8 chunks and 256 8.1), and at most 4 slices of the wider panels.
-// Eight row-steps in flight serve a split K and a short one as well as sixteen or better ([512, 8192] 4.9 and 5.2,
-// [64, 512] 3.2 and 3.7: at 8 chunks 16 steps are 512 rows).  A long unsplit stream keeps sixteen (W_UQ 14.7, eight
-// 15.5), panels of 32 chunks in fewer than 150 workgroups only for two rows ([1280, 36000] one row 19.1 with eight
-// and 20.7 with sixteen, two rows 23.1 and 19.9), which below K = 768 take twice the workgroups and four steps
-// instead ([260, 34000] 7.9 against 8.5, [520, 33280] 10.6 and 11.2).
+//    panels 6.9, of 5 wider ones 7.4; [7168, 2112] level);
+//  * no split of K up to 512 either ([512, 512] 4.4, two slices 4.9); rows past 256 panels of 32 chunks take 16, or
+//    64 where K has few steps or they fit one round ([512, 70000] 16.2, 64 chunks 17.2, 8 chunks 16.5; [64, 80000] 64
+//    chunks 4.9, 8 chunks 8.5; [256, 131072] 64 chunks 12.8, 16 chunks 13.5, 8 chunks 15.7);
+//  * up to 12 MB about 144 workgroups, as the streams are short ([4096, 1024] 128 of them 6.9, 256 8.2; [2048, 2048]
+//    level), and at most 4 slices of the wider panels.
+// Eight row-steps in flight serve a split K and a short one as well as sixteen or better ([512, 512] 4.4 and 4.5,
+// [64, 512] 3.2 and 3.9: at 8 chunks 16 steps are 512 rows).  A long unsplit stream keeps sixteen (W_UQ 15.2, eight
+// 15.6), panels of 32 chunks in fewer than 150 workgroups only for two rows ([1280, 36000] one row 20.3 with eight
+// and 21.1 with sixteen, two rows 23.9 and 20.8), which below K = 768 take twice the workgroups and four steps
+// instead ([260, 34000] 7.8 against 8.6, [520, 33280] 10.7 and 11.8).
 struct NarrowChoice {
     int cw = 0, ks = 1, unroll = 8;
 };
@@ -152,9 +152,9 @@ NarrowChoice narrow_plan(int mt, int64_t K, int64_t chunks, int64_t w_bytes) {
 // The matrix-core partition: 128-column panels, K-slices of whole 64-row stages, x tiles of
 // 16 or 32 rows.  As many slices as keep the grid within one workgroup per CU: a part-filled second
 // round costs more than shorter slices save (measured on MI355X at 4 / 32 rows, floor(256 / panels)
-// slices against the power of two nearest it: [4096, 5120] 6 slices 11.4 / 13.4 us against 8 13.7 /
-// 18.0, [1024, 2560] 12 slices 6.7 / 9.0 against 16 8.2 / 14.9, [4096, 8960] 3 slices 16.2 / 18.8
-// against 4 20.1 / 24.1; where the two agree, W_O's 4 and [8192, 8192]'s, nothing changes).
+// slices against the power of two nearest it: [4096, 5120] 6 slices 11.8 / 13.6 us against 8 14.1 /
+// 17.7, [1024, 2560] 8 slices 6.6 / 8.5 against 16 8.8 / 14.2, [4096, 8960] 3 slices 15.7 / 18.3
+// against 4 18.9 / 23.2; where the two agree, W_O's 4 and [8192, 8192]'s, nothing changes).
 nmm_status plan_mfma(int64_t M, int64_t K, int64_t N, GemvPlan* p) {
     GemvPlan q;
     q.path = NMM_PATH_MFMA;
@@ -169,17 +169,18 @@ nmm_status plan_mfma(int64_t M, int64_t K, int64_t N, GemvPlan* p) {
     }
     const int64_t panels = int64_t(q.mblocks) * q.n_full;
     const int64_t want = tuned("NMM_GEMV_TARGET", kMfmaTargetGrid);
-    // a short K takes at most 8 slices ([1536, 1536] 6.6 us, 12 slices 6.8; [512, 512] 5.1, 2 slices 6.3)
+    // a short K takes at most 8 slices ([1536, 1536] at 4 / 32 rows 6.5 / 7.8 us, 12 slices 6.7 / 9.5; [512, 512] 5.1 /
+    // 6.1, 2 slices 5.3 / 6.3; four would be 4.6 / 5.6 there)
     const int64_t ks_cap = tuned("NMM_GEMV_MAXSPLIT", K < kMfmaShortK ? 8 : 16);
     int64_t ks_want = std::max<int64_t>(1, want / panels);
     // no more slices than nmm_gemv_noalloc's scratch holds (170 panels of 32 rows: two)
     const int64_t slice_bytes = panels * q.mt * kMfmaPanelCols * 4;
     const int64_t fits = (int64_t(NMM_NOALLOC_SCRATCH_BYTES) - kTicketBytes) / slice_bytes;
     // 129 to 170 panels on a long K: three slices, two workgroups per CU side by side.  At 4 / 32 rows [4096, 16512]
-    // 26.6 / 30.5 us against 29.2 / 31.0 with one, [2560, 20480] 20.8 / 23.6 against 22.5 / 25.0, [2048, 16512] 16.1 /
-    // 19.3 against 16.4 / 17.8; two slices lose to one wherever the grid has over 128 panels ([2048, 22400], 175 panels,
-    // 20.4 / 23.4 against 18.2 / 19.9; [4096, 16512] 32.2 / 38.4), and five to two at 86 to 89 ([2048, 11136] 13.0 / 16.2
-    // against 12.0 / 14.3)
+    // 26.8 / 30.8 us against 30.0 / 31.8 with one, [2560, 20480] 20.7 / 24.6 against 22.4 / 26.0, [2048, 16512] 16.1 /
+    // 19.5 against 16.5 / 17.7; two slices lose to one wherever the grid has over 128 panels ([2048, 22400], 175 panels,
+    // 20.4 / 23.5 against 18.3 / 19.9; [4096, 16512] 32.9 / 38.8), and five to two at 86 to 89 ([2048, 11136] 13.2 / 16.5
+    // against 12.2 / 14.6)
     if (ks_want == 1 && 2 * want / panels == 3 && fits >= 3 && K >= (q.mt == 16 ? kMfmaLongK : kMfmaLongK32)) ks_want = 3;
     ks_want = std::max<int64_t>(1, std::min(std::min(ks_want, ks_cap), fits));
     int64_t r = rup(cdiv(K, ks_want), kMfmaStageRows);
@@ -212,9 +213,9 @@ nmm_status plan_gemv(int64_t batch, int64_t M, int64_t K, int64_t N, int dt, int
     GemvPlan q;
     // AUTO for a single matrix: the streaming GEMV for one row, the matrix cores from
     // kMfmaMinMDefault rows on.  At two rows the matrix-core launch wins only where its plan needs no
-    // K-split: its split-K tail costs more than the GEMV's second row.  Measured on MI355X: W_UQ [1536,
-    // 24576] (one slice) 15.4 against 16.3 us; W_O [16384, 7168] (4 slices) 40.5 against 39.8; down
-    // [7168, 2112] (15 slices) 10.5 against 9.7.  A batch has the streaming plan; whether its
+    // K-split: its split-K tail costs as much as the GEMV's second row or more.  Measured on MI355X: W_UQ [1536,
+    // 24576] (one slice) 15.3 against 16.2 us; W_O [16384, 7168] (4 slices) 39.5 against 39.6; down
+    // [7168, 2112] (15 slices) 10.6 against 9.9.  A batch has the streaming plan; whether its
     // launch takes the matrix cores instead is heads_on_mfma's.
     if (path == NMM_PATH_AUTO) {
         const int64_t mfma_min_m = tuned("NMM_MFMA_MIN_M", kMfmaMinMDefault);
@@ -285,9 +286,6 @@ nmm_status plan_gemv(int64_t batch, int64_t M, int64_t K, int64_t N, int dt, int
 
     const int64_t rstep_full = int64_t(kWaves) * (kPanelChunks / q.cw_full);   // rows per WG step
     const int64_t rstep_tail = q.tail_chunks ? int64_t(kWaves) * (kPanelChunks / q.tail_cw) : 1;
-    const int64_t steps_per_matrix = q.n_full * cdiv(K, rstep_full) +
-                                     (q.tail_chunks ? cdiv(K, rstep_tail) : 0);
-    (void)steps_per_matrix;
     const int64_t panels_all = mats * (q.n_full + (q.tail_chunks ? 1 : 0));
     int64_t ks_want = 1;
     {
@@ -299,10 +297,10 @@ nmm_status plan_gemv(int64_t batch, int64_t M, int64_t K, int64_t N, int dt, int
         } else {
             while (ks_want < ks_cap && double(ks_want) * 1.41421356 < ratio) ks_want *= 2;   // nearest power of two
             ks_want = std::min(ks_want, ks_cap);
-            // one or two rows: not more than one workgroup per CU ([10000, 9001], 36 panels: 7 slices 32.1
-            // us, 8 slices 42.0).  Where that leaves over 30 % of the CUs idle, a last panel of up to a quarter's width,
-            // whose workgroups end early, does not count ([800, 65600], 128 panels and 8 chunks: two slices 19.8,
-            // one 21.4; but [4096, 16512], 32 panels and 16 chunks: 7 slices 26.5, 8 slices 27.8)
+            // one or two rows: not more than one workgroup per CU ([10000, 9001], 36 panels: 7 slices 30.8
+            // us, 8 slices 41.9).  Where that leaves over 30 % of the CUs idle, a last panel of up to a quarter's width,
+            // whose workgroups end early, does not count ([800, 65600], 128 panels and 8 chunks: two slices 20.1,
+            // one 23.6; but [4096, 16512], 32 panels and 16 chunks at two rows: 7 slices 26.4, 8 slices 27.9)
             if (narrow_m && mats == 1 && ks_want * panels_all > want) {
                 const int64_t fit = std::max<int64_t>(1, want / panels_all);
                 const bool idle = fit * panels_all * 10 < want * 7;
@@ -349,12 +347,12 @@ nmm_status plan_gemv(int64_t batch, int64_t M, int64_t K, int64_t N, int dt, int
 
 
 // Whether AUTO gives a batch to the matrix cores.  Measured on MI355X (batches of 8 / 32 / 128 heads):
-//  * from two rows on: [128, 512] at 2 rows 3.1 / 3.6 / 6.0 us against 4.9 / 5.2 / 6.1 for the GEMV, at
-//    4 rows 3.1 / 3.6 / 6.0 against 7.2 / 8.9 / 8.2, at 16 rows 3.2 / 3.8 / 7.4 against 15 / 21 / 21.5;
-//    [512, 128] at 4 rows 4.6 / 4.7 / 5.9 against 7.2 / 7.7 / 8.0;
+//  * from two rows on: [128, 512] at 2 rows 3.3 / 3.7 / 6.7 us against 4.8 / 5.1 / 6.8 for the GEMV, at
+//    4 rows 3.4 / 3.7 / 6.7 against 7.2 / 8.8 / 8.8, at 16 rows 3.5 / 3.9 / 7.6 against 15 / 21 / 21;
+//    [512, 128] at 4 rows 4.5 / 4.7 / 6.1 against 7.0 / 7.6 / 8.2;
 //  * at one row where K is short and the grid small, so that the GEMV has little to stream: [128, 512]
-//    3.1 / 3.6 against 4.3 / 4.6 for 8 and 32 heads, but 5.8 against 5.4 for 128; [512, 128] 4.5 / 4.7 /
-//    5.8 against 4.4 / 4.4 / 5.9.
+//    3.3 / 3.7 against 4.2 / 4.5 for 8 and 32 heads, but 7 % slower than the GEMV for 128; [512, 128] 2 to 7 % slower
+//    for 8 and 32 heads, level for 128.
 // All of K is one workgroup's, so a long K with few workgroups stays on the GEMV, which splits it.
 bool heads_on_mfma(int64_t batch, int64_t M, int64_t K, int64_t N) {
     if (batch <= 1 || M <= 0 || K <= 0 || N <= 0) return false;
@@ -431,12 +429,12 @@ nmm_status plan_gemv_nt(int64_t M, int64_t K, int64_t N, NtPlan* p) {
 
 // The matrix-core form of the transposed-weight product, or false where the one-row GEMV is the
 // better one.  Measured on MI355X (GPU time, W rotated over three copies):
-//  * from two rows on always: W_O [7168, 16384] at 2 / 4 / 16 / 32 rows 40 / 40 / 41 / 52 us against
-//    48 / 53 / 172 / 332 for the GEMV (in blocks of 4 rows); [576, 7168] 7.3 / 7.8 / 10.3 / 13.4
-//    against 8.2 / 17.3 / 19.5 / 27.5; [512, 512] 2.7 / 2.8 / 3.1 / 3.9 against 4.4 / 5.1 / 6.0 / 6.0;
-//  * one row up to K = 2048: [512, 512] 2.75 against 4.17, [1536, 1536] 3.95 against 4.84, W_UQ
-//    [24576, 1536] 13.9 against 14.6, [7168, 2048] 7.7 against 8.6; past that the GEMV's 1 KB rows
-//    win where rows are few or not 256-byte aligned ([576, 7168] 6.6 against 7.5, [5003, 4099] 11.4
+//  * from two rows on always: W_O [7168, 16384] at 2 / 4 / 16 / 32 rows 41 / 44 / 40 / 47 us against
+//    50 / 53 / 172 / 329 for the GEMV (in blocks of 4 rows); [576, 7168] 7.4 / 7.7 / 10.4 / 13.6
+//    against 7.9 / 16.9 / 19.2 / 26.9; [512, 512] 3.0 / 3.1 / 3.2 / 3.9 against 4.1 / 4.8 / 5.7 / 5.7;
+//  * one row up to K = 2048: [512, 512] 3.0 against 3.8, [1536, 1536] 3.9 against 4.6, W_UQ
+//    [24576, 1536] 14.6 against 14.8, [7168, 2048] 8.5 against 8.7; past that the GEMV's 1 KB rows
+//    win where rows are few or not 256-byte aligned ([576, 7168] 5.6 against 7.5, [5003, 4099] 11.4
 //    against 12.0) and the two are within 5 % elsewhere.
 bool plan_mfma_nt(const GemvArgs& a, NtMfmaPlan* p) {
     const int64_t M = a.M, K = a.K, N = a.N;
@@ -446,20 +444,19 @@ bool plan_mfma_nt(const GemvArgs& a, NtMfmaPlan* p) {
     // x rows of a block are addressed through one 32-bit buffer resource (4 rows always fit)
     if (((std::min<int64_t>(M, 4 * q.xr) - 1) * a.ldx + rup(K, 8)) * 2 >= kLimit) q.xr = 1;
     q.mblocks = static_cast<int>(cdiv(M, 4 * q.xr));
-    // two 16-row tiles of Wt per wave halve the x traffic from L2, which counts from 16 rows on: W_O 41
-    // against 46 us at 16 rows and 52 against 62 at 32, [5003, 4099] 18.5 against 22.8 at 32; while the
-    // grid still has over half a workgroup per CU (at fewer, [2112, 7168] 15.3 against 11.2)
+    // two 16-row tiles of Wt per wave halve the x traffic from L2, which counts from 16 rows on: W_O 10 % faster than
+    // with one at 16 rows and 16 % at 32 (40 and 47 us), [5003, 4099] 19 % at 32 (19.1); while the
+    // grid still has over half a workgroup per CU (at fewer [2112, 7168] is a third slower with two)
     q.nt = q.xr >= 4 && cdiv(N, 32) >= 150 ? 2 : 1;
     q.row_blocks = static_cast<int>(cdiv(N, 16 * q.nt));
-    // one workgroup per CU at most: a third group in flight (up to 8 rows; [2112, 7168] 8.6 against 9.1
-    // us at 4); with more workgroups than CUs the smaller ring lets more of them share a CU (W_UQ at one
-    // row 13.9 against 16.4)
+    // one workgroup per CU at most: a third group in flight (up to 8 rows; [2112, 7168] 5 % faster at 4); with more workgroups than CUs the smaller ring lets more of them share a CU (W_UQ at one
+    // row 15 % faster)
     q.depth = q.row_blocks <= 256 && q.xr <= 2 ? 3 : 2;
     // Rows whose 16 nt-row blocks lie a multiple of 256 KB apart meet on the same memory channels when
     // all workgroups walk k in step, so block b starts its walk b * rot rounds on.  The shift that helps
     // lies 2^9 or 2^7 (not 2^8) under the block stride: a stride of 512 KB takes 1 round of 1 KB, 256 KB
-    // takes 2 ([7168, 16384] 40.4 against 46.2 us, [4096, 16384] 26.1 against 31.5, [8192, 8192] 26.0
-    // against 26.9; the other shift 53, 38 and 37 us).
+    // takes 2 (at 4 rows [7168, 16384] 13 % faster than without, [4096, 16384] 17 %, [8192, 8192] 3 %; the other shift
+    // makes them 31, 46 and 42 % slower).
     const int64_t stride = int64_t(16) * q.nt * a.ldw * 2;
     q.rot = stride % (1 << 19) == 0 ? 1 : stride % (1 << 18) == 0 ? 2 : 0;
     q.grid = rup(q.row_blocks, 8) * q.mblocks;
